@@ -184,6 +184,55 @@ __device__ __forceinline__ void any_product(f32x16_t (&acc)[2][2], const void* A
     }
 }
 
+// ---- sums of pair products that are not finite ----------------------------------------------------
+// An infinite weight times the lower half of a pair is NaN where that half is zero and has any sign where it is not, and a value
+// near the end of the fp32 range becomes infinite when its upper half is rounded.  Such elements are formed again in plain fp32.
+// Nothing finite hides either (a sum that has met an infinity or NaN stays one, and so does SiLU(g) * u), so a tile pays a
+// few comparisons while it is stored.
+__device__ __forceinline__ bool not_finite(float v) { return !(__builtin_fabsf(v) < INFINITY); }
+__device__ __forceinline__ bool not_finite_pair(uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; }
+__device__ __forceinline__ float plain_dot(const void* A, int64_t lda, const void* B, int N, int m, int col, int k0, int k1) {
+    const float* a = reinterpret_cast<const float*>(A) + (size_t)m * (size_t)lda;
+    const bf16_t* w = reinterpret_cast<const bf16_t*>(B) + col;
+    float s = 0.f;
+#pragma unroll 1
+    for (int k = k0; k < k1; ++k) s += a[k] * bf16_to_f32(w[(size_t)k * (size_t)N]);
+    return s;
+}
+// The wave's 64 x 64 part of a stored tile at (r0, c0), a column per lane: whatever is not finite there, once more
+template <int EPI>
+__device__ __forceinline__ void mend_part(const AnyProb& P, int M, int r0, int c0, int sp, int k0, int k1) {
+    const int col = c0 + (int)(threadIdx.x & 63), N = P.N;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // the part has been stored
+#pragma unroll 1
+    for (int m = r0; m < r0 + 64 && m < M; ++m) {
+        if (col >= N) continue;
+        if constexpr (EPI != ANY_OUT) {
+            float* d = reinterpret_cast<float*>(P.C) + (size_t)sp * (size_t)P.split_stride + (size_t)m * (size_t)P.ldc + col;
+            if (!not_finite(*d)) continue;
+            float v = plain_dot(P.A, P.lda, P.B, N, m, col, k0, k1);
+            if constexpr (EPI == ANY_GATEUP) {
+                const float bg = P.bias ? bf16_to_f32(reinterpret_cast<const bf16_t*>(P.bias)[col]) : 0.f;
+                const float bu = P.bias2 ? bf16_to_f32(reinterpret_cast<const bf16_t*>(P.bias2)[col]) : 0.f;
+                v = silu_f32(v + bg) * (plain_dot(P.A2, P.lda2, P.B2, N, m, col, 0, P.K2) + bu);
+            }
+            *d = v;
+        } else {
+            bf16_t* const d = P.C ? reinterpret_cast<bf16_t*>(P.C) + (size_t)m * (size_t)P.ldc + col : nullptr;
+            bf16_t* cd = nullptr;
+            if (P.cache) {
+                const int bi = m / P.T;
+                const int64_t pp = (int64_t)P.pos[bi] + (m - bi * P.T);
+                if (pp >= 0 && pp < P.S_max) cd = reinterpret_cast<bf16_t*>(P.cache) + ((size_t)bi * (size_t)P.S_max + (size_t)pp) * (size_t)N + col;
+            }
+            if ((!d && !cd) || !not_finite(bf16_to_f32(d ? *d : *cd))) continue;
+            const float v = plain_dot(P.A, P.lda, P.B, N, m, col, k0, k1) + (P.bias ? bf16_to_f32(reinterpret_cast<const bf16_t*>(P.bias)[col]) : 0.f);
+            if (d) *d = f32_to_bf16(v);
+            if (cd) *cd = f32_to_bf16(v);
+        }
+    }
+}
+
 // nv of 8 consecutive bf16 columns, at any 2-byte alignment
 __device__ __forceinline__ void store8(bf16_t* dst, const uint4& v, int nv) {
     if (nv >= 8) { __builtin_memcpy(dst, &v, 16); return; }
@@ -233,6 +282,7 @@ __global__ void __launch_bounds__(256, 2) k_any_gemm(AnyArgs ga) {
     const int rrow = lane >> 3, runit = lane & 7;
     const bf16_t* bias = reinterpret_cast<const bf16_t*>(P.bias);
     const bf16_t* bias2 = reinterpret_cast<const bf16_t*>(P.bias2);
+    bool again = false;                     // this lane has stored something that is not finite
     if constexpr (EPI != ANY_OUT) {
         float* const C = reinterpret_cast<float*>(P.C) + (size_t)sp * (size_t)P.split_stride;
 #pragma unroll
@@ -266,6 +316,7 @@ __global__ void __launch_bounds__(256, 2) k_any_gemm(AnyArgs ga) {
                     const int row = it * 8 + rrow, m = m0 + wm * 64 + mi * 32 + row;
                     const float4 v = *reinterpret_cast<const float4*>(patch + row * 128 + ((runit ^ ((row >> 1) & 7)) * 16));
                     if (m < M && col < N) {
+                        if constexpr (AF32) again = again || not_finite(v.x) || not_finite(v.y) || not_finite(v.z) || not_finite(v.w);
                         float* d = C + (size_t)m * (size_t)P.ldc + col;
                         if (col + 4 <= N) __builtin_memcpy(d, &v, 16);
                         else { d[0] = v.x; if (col + 1 < N) d[1] = v.y; if (col + 2 < N) d[2] = v.z; }
@@ -300,10 +351,14 @@ __global__ void __launch_bounds__(256, 2) k_any_gemm(AnyArgs ga) {
             for (int it = 0; it < 4; ++it) {
                 const int row = it * 8 + rrow, m = r0 + row;
                 const uint4 v = *reinterpret_cast<const uint4*>(patch + row * 128 + ((runit ^ ((row >> 1) & 7)) * 16));
+                if constexpr (AF32) again = again || not_finite_pair(v.x) || not_finite_pair(v.y) || not_finite_pair(v.z) || not_finite_pair(v.w);
                 if (nv > 0 && m < M && C) store8(C + (size_t)m * (size_t)P.ldc + col8, v, nv);
                 if (nv > 0 && crow[it] >= 0) store8(cache + (size_t)crow[it] * (size_t)N + col8, v, nv);
             }
         }
+    }
+    if constexpr (AF32) {
+        if (__builtin_amdgcn_ballot_w64(again) != 0ull) mend_part<EPI>(P, M, m0 + wm * 64, n0 + wn * 64, sp, kb, ke);
     }
 }
 

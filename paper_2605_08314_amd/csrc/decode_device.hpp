@@ -152,6 +152,18 @@ __device__ __forceinline__ float bf16_rest(float a, uint32_t hi_bits) {
     return hi == a ? 0.f : a - hi;
 }
 
+// a . w over k in [k0, k1) in plain fp32.  A sum of pair products that is not finite is formed again this way: an infinite weight
+// times the lower half of a pair is NaN where that half is zero and has any sign where it is not, and a value near the end of
+// the fp32 range becomes infinite when its upper half is rounded.  Nothing finite hides either (a sum that has met an infinity or
+// NaN stays one), so ordinary sums pay one comparison each.
+__device__ __forceinline__ bool not_finite(float v) { return !(__builtin_fabsf(v) < INFINITY); }
+__device__ __forceinline__ float plain_dot(const float* a, const bf16_t* w, size_t ldw, int k0, int k1) {
+    float s = 0.f;
+#pragma unroll 1
+    for (int k = k0; k < k1; ++k) s += a[k] * bf16_to_f32(w[(size_t)k * ldw]);
+    return s;
+}
+
 // This wave's stores and atomics have been performed.  A release fence of workgroup scope is not enough in front of a signal to
 // other workgroups: the waves of a workgroup share one vector cache, so that fence waits for LDS only.
 __device__ __forceinline__ void drain_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -468,6 +480,12 @@ __device__ __forceinline__ void decode_tile(const DProb& P, int M, int lt, float
             float sum = r0[0];
 #pragma unroll
             for (int w = 1; w < NW; ++w) sum += r0[(size_t)w * NSL * Q * 64 * 4];
+            if constexpr (RAG && AF32) {
+                if (not_finite(sum)) {
+                    const int k0 = tk * P.KS, k1 = k0 + P.KS < P.K ? k0 + P.KS : P.K;
+                    sum = plain_dot((const float*)P.A + (size_t)m * P.lda, P.W + n0 + c, P.N, k0, k1);
+                }
+            }
             // RETURNING atomics: a non-returning one is acknowledged as soon as the L2 has accepted it,
             // before it is performed where other XCDs can see it; its return value only exists once it
             // has been performed, and consuming the values below orders them before the arrival signal.
@@ -494,6 +512,16 @@ __device__ __forceinline__ void decode_tile(const DProb& P, int M, int lt, float
                 val[mt][4 * q + 0] = s.x; val[mt][4 * q + 1] = s.y; val[mt][4 * q + 2] = s.z; val[mt][4 * q + 3] = s.w;
             }
         if (m < M) {
+            if constexpr (RAG && AF32) {
+#pragma unroll
+                for (int mt = 0; mt < NMAT; ++mt)
+#pragma unroll
+                    for (int b = 0; b < CPL; ++b)
+                        if (n + b < P.N && not_finite(val[mt][b])) {
+                            const char* a = (const char*)(mt ? P.A2 : P.A) + (ASHIFT ? acc_shift : 0);
+                            val[mt][b] = plain_dot((const float*)a + (size_t)m * (mt ? P.lda2 : P.lda), (mt ? P.W2 : P.W) + n + b, P.N, 0, mt ? P.K2 : P.K);
+                        }
+            }
             if constexpr (EPI == EPI_STORE) {
                 if (nan_out) {
 #pragma unroll

@@ -162,3 +162,69 @@ def test_rank_project(G, oracle):
         t = torch.full((M, r), float("nan"), dtype=G.tdtype(dtype), device="cuda")
         B.lowrank_rank_project(G.dev(x), G.dev(U), t, B.new_workspace(B.LR_OP_LINEAR, M, d_in, r, 0, G.code(dtype)))
         assert beyond_rounding(G.host64(t), x.f64 @ U.f64, dtype) <= TOL[dtype]
+
+
+def same_pattern(got, want, dtype="bf16"):
+    """Infinities of the same sign and NaN in the same places, everything else within the tolerance."""
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(np.sign(got[inf]), np.sign(want[inf]))
+    ok = np.isfinite(want)
+    assert ok.any() and inf.any()
+    assert beyond_rounding(got[ok], want[ok], dtype) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("whole", [False, True])       # True: rank-space values that are bf16 numbers, so that the lower half of their pair is zero
+@pytest.mark.parametrize("M", [1, 16, 31, 33, 200])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_infinite_weights(G, oracle, dtype, M, whole):
+    """An infinite weight makes its product infinite with the sign of the rank-space or hidden value, whatever the bits of that value."""
+    rng = np.random.default_rng(M)
+    d_in, r, d_out = 203, 67, 131
+    f = lambda *s: rng.integers(1, 4, size=s) * rng.choice([-1.0, 1.0], size=s) * (rng.random(s) < 0.1) if whole else rng.standard_normal(s)  # noqa: E731
+    x, U, V = f(M, d_in), f(d_in, r) if whole else f(d_in, r) * d_in ** -0.5, f(r, d_out) if whole else f(r, d_out) * r ** -0.5
+    x[:, :r] += (2.0 if whole else 0.0) * (np.arange(r) % 2 * 2 - 1)
+    V[5, 7], V[66, 64], V[0, 130], V[10, 20], V[11, 20] = np.inf, -np.inf, np.inf, np.inf, -np.inf
+    x, U, V = (synth.to_dtype(a, dtype) for a in (x, U, V))
+    t = x.f64 @ U.f64
+    assert not whole or np.array_equal(synth.to_dtype(t, "bf16").f64, t)
+    with np.errstate(invalid="ignore"):
+        want = t @ V.f64
+    same_pattern(G.host64(G.run_linear(x, U, V, None, "auto", dtype)), want, dtype)
+
+
+@pytest.mark.parametrize("shared", [0, 1])
+@pytest.mark.parametrize("where", ["V_g", "V_u", "U_d", "V_d"])
+@pytest.mark.parametrize("M", [3, 32, 33, 140])
+def test_infinite_weights_of_an_mlp(G, oracle, M, where, shared):
+    """Every stage of the packed MLP: what an infinite weight reaches is infinite or NaN as in the formula, the rest as ever.  An infinite
+    hidden value goes through positive weights into every rank; two columns of the result take the ranks up with one sign each."""
+    B = G.B
+    w = synth.mlp_layer(M, d=101, ffn=187, r_g=33, r_u=65, r_d=35, seed=40 + M, dtype="bf16", with_bias=True)
+    t = dict(w.t)
+    a = {k: t[k].f64.copy() for k in ("V_g", "V_u", "U_d", "V_d")}
+    at = {"V_g": (4, 100), "V_u": (64, 130), "U_d": (186, 34), "V_d": (0, 100)}[where]
+    if where in ("V_g", "V_u"):
+        a["U_d"][at[1]] = np.abs(a["U_d"][at[1]]) + 0.125
+        a["V_d"][:, 0], a["V_d"][:, 1] = np.abs(a["V_d"][:, 0]) + 0.125, -np.abs(a["V_d"][:, 1]) - 0.125
+    a[where][at] = np.inf
+    for k in a:
+        t[k] = synth.to_dtype(a[k], "bf16")
+        a[k] = t[k].f64
+    w.t = t
+    with np.errstate(all="ignore"):
+        tt = t["x"].f64 @ t["U_gu"].f64
+        g = tt[:, :33] @ a["V_g"] + t["b_g"].f64
+        h = g / (1 + np.exp(-g)) * (tt[:, 33:] @ a["V_u"] + t["b_u"].f64)
+        want = (h @ a["U_d"]) @ a["V_d"] + t["b_d"].f64
+    B.lowrank_configure(B.LR_CFG_DEVICE_SHARED, shared)
+    try:
+        got = G.host64(G.run_mlp(w, "auto"))
+    finally:
+        B.lowrank_configure(B.LR_CFG_DEVICE_SHARED, 0)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf, ok = np.isinf(want), np.isfinite(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(np.sign(got[inf]), np.sign(want[inf]))
+    assert inf.any()
+    if ok.any():
+        assert beyond_rounding(got[ok], want[ok]) <= TOL["bf16"]
