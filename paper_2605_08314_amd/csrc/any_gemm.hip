@@ -7,12 +7,12 @@
 // per CU cover each other's barriers.
 //
 // Bound by the matrix cores and the register path around them.  Measured: a layer of 1500 rows at d = 4096, ffn = 11008, ranks
-// 371 / 755 with its attention 569 us (one thread per output element before: 40.3 ms); of that gate/up 199 us = 0.50 PFLOP/s
-// of matrix work, h U_d 75 us = 0.66 PFLOP/s.
+// 371 / 755 with its attention 643 us (one thread per output element before: 40.3 ms).
 //
-// Precision: rank-space and hidden rows stay fp32 between the launches.  Such an operand is split on its way into LDS into a
-// bf16 pair hi + lo (2^-17 of the value) and multiplied in two matrix instructions per fragment pair, so that only the
-// result is rounded to bf16.  B is read once for both.
+// Precision: rank-space and hidden rows stay fp32 between the launches.  Such an operand is cut on its way into LDS into three
+// bf16 parts that add up to all its 24 bits and multiplied in three matrix instructions per fragment pair, so that only the
+// result is rounded to bf16.  B is read once for all three.  (Two parts keep 16 bits: 4.5e-6 of the result before its rounding,
+// where plain fp32 is off by less than 1e-6; the layer above took 568 us with them.)
 #include "any.hpp"
 #include "decode.hpp"
 #include "prefill_device.hpp"
@@ -21,7 +21,8 @@ namespace lr {
 
 constexpr int ABM = kAnyTile, ABN = kAnyTile, ABK = kAnyStep;
 constexpr int kATile = ABM * ABK * 2, kBTile = ABK * ABN * 2;         // bytes of a bf16 tile in LDS
-template <bool AF32> constexpr int any_stage_bytes() { return kATile + kBTile + (AF32 ? kATile : 0); }   // A (hi) | B | A lo
+constexpr int kRest = kATile + kBTile;                                // a stage: A (first part) | B | A second part | A third part
+template <bool AF32> constexpr int any_stage_bytes() { return kRest + (AF32 ? 2 * kATile : 0); }
 
 // One thread's share of a step: two 8-k units of A (fp32: 32 bytes each), two 8-column units of B.
 template <bool AF32> struct AnyRegs { uint4 a[AF32 ? 4 : 2]; uint4 b[2]; };
@@ -33,11 +34,6 @@ struct AnyOperands {
     int64_t avail;               // elements of B from `B` to the matrix's end
     int K;
 };
-
-__device__ __forceinline__ uint32_t rest_pair(float x, float y, uint32_t h) {
-    const float hx = __uint_as_float(h << 16), hy = __uint_as_float(h & 0xffff0000u);
-    return ppack2(hx == x ? 0.f : x - hx, hy == y ? 0.f : y - hy);        // (an infinity has no rest)
-}
 
 template <bool AF32>
 __device__ __forceinline__ void any_load(AnyRegs<AF32>& r, const AnyOperands& o, int k0) {
@@ -100,13 +96,14 @@ __device__ __forceinline__ void any_write(const AnyRegs<AF32>& r, char* stage) {
         char* p = stage + row * 64 + ((c ^ ((row >> 2) & 3)) * 16);
         if constexpr (AF32) {
             const uint4 u = r.a[2 * j], v = r.a[2 * j + 1];
-            const float f[8] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w),
-                                __uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-            uint4 h, l;
-            h.x = ppack2(f[0], f[1]); h.y = ppack2(f[2], f[3]); h.z = ppack2(f[4], f[5]); h.w = ppack2(f[6], f[7]);
-            l.x = rest_pair(f[0], f[1], h.x); l.y = rest_pair(f[2], f[3], h.y); l.z = rest_pair(f[4], f[5], h.z); l.w = rest_pair(f[6], f[7], h.w);
-            *reinterpret_cast<uint4*>(p) = h;
-            *reinterpret_cast<uint4*>(p + kATile + kBTile) = l;
+            float f[8] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w),
+                          __uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+                uint4 o;
+                o.x = bf16_part(f[0], f[1]); o.y = bf16_part(f[2], f[3]); o.z = bf16_part(f[4], f[5]); o.w = bf16_part(f[6], f[7]);
+                *reinterpret_cast<uint4*>(p + (part == 0 ? 0 : kRest + (part - 1) * kATile)) = o;
+            }
         } else {
             *reinterpret_cast<uint4*>(p) = r.a[j];
         }
@@ -122,22 +119,15 @@ template <bool AF32>
 __device__ __forceinline__ void any_compute(f32x16_t (&acc)[2][2], const char* stage, const FragAddr<ABM, ABN, 22>& f) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
-        bf16x8_t a[2], al[2], b[2];
-        a[0] = dma_read_a<ABM, ABN, 22, 0>(stage, f, kk); b[0] = dma_read_b<ABM, ABN, 22, 0>(stage, f, kk);
-        b[1] = dma_read_b<ABM, ABN, 22, 1>(stage, f, kk); a[1] = dma_read_a<ABM, ABN, 22, 1>(stage, f, kk);
-        if constexpr (AF32) {
-            al[0] = dma_read_a<ABM, ABN, 22, 0>(stage + kATile + kBTile, f, kk);
-            al[1] = dma_read_a<ABM, ABN, 22, 1>(stage + kATile + kBTile, f, kk);
-        }
+        const bf16x8_t b[2] = {dma_read_b<ABM, ABN, 22, 0>(stage, f, kk), dma_read_b<ABM, ABN, 22, 1>(stage, f, kk)};
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ni], a[mi], acc[mi][ni], 0, 0, 0);
-        if constexpr (AF32) {
+        for (int part = 0; part < (AF32 ? 3 : 1); ++part) {
+            const char* at = stage + (part == 0 ? 0 : kRest + (part - 1) * kATile);
+            const bf16x8_t a[2] = {dma_read_a<ABM, ABN, 22, 0>(at, f, kk), dma_read_a<ABM, ABN, 22, 1>(at, f, kk)};
 #pragma unroll
             for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ni], al[mi], acc[mi][ni], 0, 0, 0);
+                for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ni], a[mi], acc[mi][ni], 0, 0, 0);
         }
     }
 }
@@ -184,9 +174,9 @@ __device__ __forceinline__ void any_product(f32x16_t (&acc)[2][2], const void* A
     }
 }
 
-// ---- sums of pair products that are not finite ----------------------------------------------------
-// An infinite weight times the lower half of a pair is NaN where that half is zero and has any sign where it is not, and a value
-// near the end of the fp32 range becomes infinite when its upper half is rounded.  Such elements are formed again in plain fp32.
+// ---- sums of products in parts that are not finite ------------------------------------------------
+// An infinite weight times a part that is zero is NaN, and so is every weight times an infinite value's rest.  Such elements are
+// formed again in plain fp32.
 // Nothing finite hides either (a sum that has met an infinity or NaN stays one, and so does SiLU(g) * u), so a tile pays a
 // few comparisons while it is stored.
 __device__ __forceinline__ bool not_finite(float v) { return !(__builtin_fabsf(v) < INFINITY); }
@@ -245,11 +235,11 @@ __device__ __forceinline__ void store8(bf16_t* dst, const uint4& v, int nv) {
 template <bool AF32, int EPI>
 __global__ void __launch_bounds__(256, 2) k_any_gemm(AnyArgs ga) {
     constexpr int SB = any_stage_bytes<AF32>();
-    __shared__ uint4 lds[(2 * SB + 4 * 4096) / 16];
+    __shared__ uint4 lds[2 * SB / 16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     char* ring = reinterpret_cast<char*>(lds);
-    char* patch = ring + 2 * SB + wave * 4096;
+    char* patch = ring + wave * 4096;                              // (the products leave the ring through a barrier)
     // workgroups go to the 8 XCDs round-robin: give each XCD a contiguous run of tiles
     const int per = (ga.total + 7) >> 3;
     const int id = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);

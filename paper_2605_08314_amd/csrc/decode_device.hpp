@@ -73,9 +73,11 @@ __device__ __forceinline__ void st_coherent_b64(void* p, uint2 v) {
 //                last column reads on into the next row, which feeds only columns that are never stored; loads that would
 //                pass the end of the matrix are moved back to its last four elements and put right before their use
 //   activations  likewise, and the block that contains the end of a row zero-fills k >= K
-//   precision    rank-space and hidden rows stay fp32 between the stages and enter the matrix cores as a bf16 pair
-//                hi + lo (two instructions per block: the stages are bound by the weight bytes, not by them), so that only the
-//                result is rounded to bf16
+//   precision    rank-space and hidden rows stay fp32 between the stages and enter the matrix cores as three bf16 parts that
+//                add up to all 24 bits (three instructions per block: the stages are bound by the weight bytes, not by them), so
+//                that only the result is rounded to bf16.  (Two parts keep 16 bits -- 4.5e-6 of the result before its rounding, where
+//                plain fp32 is off by less than 1e-6 -- and are no faster: 29.7 us against 29.8 for the packed MLP of 5 rows at
+//                ranks 701 / 746 / 659.)
 template <int CPL>
 __device__ __forceinline__ void load_w_rag(WFrag<CPL>& f, const bf16_t* __restrict__ W, int N, int kb, int g, int col, int64_t avail) {
     static_assert(CPL == 4, "64-column tiles");
@@ -146,18 +148,12 @@ __device__ __forceinline__ void load_a_rag(AFrag<AF32>& f, const void* A, int ld
     }
 }
 
-// what is left of a after its rounding to bf16 (zero for an infinity, whose difference would be NaN)
-__device__ __forceinline__ float bf16_rest(float a, uint32_t hi_bits) {
-    const float hi = __uint_as_float(hi_bits);
-    return hi == a ? 0.f : a - hi;
-}
-
-// a . w over k in [k0, k1) in plain fp32.  A sum of pair products that is not finite is formed again this way: an infinite weight
-// times the lower half of a pair is NaN where that half is zero and has any sign where it is not, and a value near the end of
-// the fp32 range becomes infinite when its upper half is rounded.  Nothing finite hides either (a sum that has met an infinity or
-// NaN stays one), so ordinary sums pay one comparison each.
+// a . w over k in [k0, k1) in plain fp32.  A sum of products in parts that is not finite is formed again this way: an infinite
+// weight times a part that is zero is NaN, and so is every weight times an infinite value's rest.  Nothing finite hides either (a
+// sum that has met an infinity or NaN stays one), so ordinary sums pay one comparison each.  (Out of line: inlined at each of its
+// uses the same packed MLP takes 30.6 us.)
 __device__ __forceinline__ bool not_finite(float v) { return !(__builtin_fabsf(v) < INFINITY); }
-__device__ __forceinline__ float plain_dot(const float* a, const bf16_t* w, size_t ldw, int k0, int k1) {
+__device__ __noinline__ float plain_dot(const float* a, const bf16_t* w, size_t ldw, int k0, int k1) {
     float s = 0.f;
 #pragma unroll 1
     for (int k = k0; k < k1; ++k) s += a[k] * bf16_to_f32(w[(size_t)k * ldw]);
@@ -197,46 +193,57 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(uint32_t a, uint32_t b, uint32_t c
     return x.v;
 }
 
+// dword s of the operand = { row 2s (low half), row 2s+1 (high half) } of column b
+template <int CPL>
+__device__ __forceinline__ bf16x8_t w_operand(const WFrag<CPL>& wf, int b) {
+    const int q = b >> 1;
+    const uint32_t sel = (b & 1) ? 0x07060302u : 0x05040100u;   // pick the high / low bf16 of each dword
+    return as_bf16x8(__builtin_amdgcn_perm(wf.w[1][q], wf.w[0][q], sel), __builtin_amdgcn_perm(wf.w[3][q], wf.w[2][q], sel),
+                     __builtin_amdgcn_perm(wf.w[5][q], wf.w[4][q], sel), __builtin_amdgcn_perm(wf.w[7][q], wf.w[6][q], sel));
+}
+
 // acc[mb][b] += A_mb (16 x 32) * W(:, column offset b) (32 x 16 lanes)
 template <int MB, int CPL, bool AF32, bool RAG = false>
 __device__ __forceinline__ void mma_block(f32x4_t (&acc)[MB][CPL], const WFrag<CPL>& wf, const AFrag<AF32> (&af)[MB]) {
-    bf16x8_t av[MB], al[MB];
-    constexpr bool kPair = RAG && AF32;         // fp32 activations as a bf16 pair
+    if constexpr (RAG && AF32) {
+        // part after part, each against all columns: the rests stay in the activations' registers
+        bf16x8_t bv[CPL];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        if constexpr (AF32) {
-            const uint32_t* a = af[mb].a;
-            const uint32_t h0 = pack2(__uint_as_float(a[0]), __uint_as_float(a[1])), h1 = pack2(__uint_as_float(a[2]), __uint_as_float(a[3]));
-            const uint32_t h2 = pack2(__uint_as_float(a[4]), __uint_as_float(a[5])), h3 = pack2(__uint_as_float(a[6]), __uint_as_float(a[7]));
-            av[mb] = as_bf16x8(h0, h1, h2, h3);
-            if constexpr (kPair) {
-                const uint32_t h[4] = {h0, h1, h2, h3};
-                uint32_t l[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    l[i] = pack2(bf16_rest(__uint_as_float(a[2 * i]), h[i] << 16), bf16_rest(__uint_as_float(a[2 * i + 1]), h[i] & 0xffff0000u));
-                al[mb] = as_bf16x8(l[0], l[1], l[2], l[3]);
-            }
-        } else {
-            av[mb] = as_bf16x8(af[mb].a[0], af[mb].a[1], af[mb].a[2], af[mb].a[3]);
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < CPL; ++b) {
-        const int q = b >> 1;
-        const uint32_t sel = (b & 1) ? 0x07060302u : 0x05040100u;   // pick the high / low bf16 of each dword
-        // dword s of the operand = { row 2s (low half), row 2s+1 (high half) } of column b
-        const bf16x8_t bv = as_bf16x8(__builtin_amdgcn_perm(wf.w[1][q], wf.w[0][q], sel),
-                                      __builtin_amdgcn_perm(wf.w[3][q], wf.w[2][q], sel),
-                                      __builtin_amdgcn_perm(wf.w[5][q], wf.w[4][q], sel),
-                                      __builtin_amdgcn_perm(wf.w[7][q], wf.w[6][q], sel));
+        for (int b = 0; b < CPL; ++b) bv[b] = w_operand<CPL>(wf, b);
+        float a[MB][8];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
-            acc[mb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mb], bv, acc[mb][b], 0, 0, 0);
-        if constexpr (kPair) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a[mb][i] = __uint_as_float(af[mb].a[i]);
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                uint32_t p[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[i] = bf16_part(a[mb][2 * i], a[mb][2 * i + 1]);
+                const bf16x8_t av = as_bf16x8(p[0], p[1], p[2], p[3]);
+#pragma unroll
+                for (int b = 0; b < CPL; ++b) acc[mb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[b], acc[mb][b], 0, 0, 0);
+            }
+    } else {
+        bf16x8_t av[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            if constexpr (AF32) {
+                const uint32_t* a = af[mb].a;
+                av[mb] = as_bf16x8(pack2(__uint_as_float(a[0]), __uint_as_float(a[1])), pack2(__uint_as_float(a[2]), __uint_as_float(a[3])),
+                                   pack2(__uint_as_float(a[4]), __uint_as_float(a[5])), pack2(__uint_as_float(a[6]), __uint_as_float(a[7])));
+            } else {
+                av[mb] = as_bf16x8(af[mb].a[0], af[mb].a[1], af[mb].a[2], af[mb].a[3]);
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < CPL; ++b) {
+            const bf16x8_t bv = w_operand<CPL>(wf, b);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
-                acc[mb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mb], bv, acc[mb][b], 0, 0, 0);
+                acc[mb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mb], bv, acc[mb][b], 0, 0, 0);
         }
     }
 }
@@ -326,6 +333,8 @@ __device__ __forceinline__ void mma_range(f32x4_t (&acc)[MB][CPL], const bf16_t*
 // Gate/up tiles: the blocks of both products as ONE sequence (nb1 blocks of W, then nb2 blocks of W2; this wave takes
 // entries wave, wave + NW, ...), so that the prefetch runs across the border between the two products.  Two ranges one
 // after the other let the requests drain at the end of the first: a memory latency per tile with nothing in flight.
+// RAG: one load behind selected operands, not a branch with the loads of either product, which holds the addresses of both (352
+// bytes a lane spilled from 17 rows on).
 template <int MB, int CPL, bool AF32, int PF, int NW, bool RAG, class Sync>
 __device__ __forceinline__ void mma_range2(f32x4_t (&acc1)[MB][CPL], f32x4_t (&acc2)[MB][CPL],
                                            const bf16_t* __restrict__ W, const bf16_t* __restrict__ W2, int N,
@@ -339,8 +348,9 @@ __device__ __forceinline__ void mma_range2(f32x4_t (&acc1)[MB][CPL], f32x4_t (&a
     for (int p = 0; p < PF; ++p) {
         const int v = blk + NW * p;
         if (v < nv) {
-            if (v < nb1) load_w_block<CPL, RAG>(wf[p], W, N, v, g, col, avail);
-            else         load_w_block<CPL, RAG>(wf[p], W2, N, v - nb1, g, col, avail2);
+            if constexpr (RAG) load_w_rag<CPL>(wf[p], v < nb1 ? W : W2, N, v < nb1 ? v : v - nb1, g, col, v < nb1 ? avail : avail2);
+            else if (v < nb1) load_w_block<CPL, RAG>(wf[p], W, N, v, g, col, avail);
+            else load_w_block<CPL, RAG>(wf[p], W2, N, v - nb1, g, col, avail2);
         }
     }
     sync(late_err);
@@ -350,8 +360,9 @@ __device__ __forceinline__ void mma_range2(f32x4_t (&acc1)[MB][CPL], f32x4_t (&a
         if (v < nv) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
-                if (v < nb1) load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A, lda, 16 * mb + j, M, v, g, K);
-                else         load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A2, lda2, 16 * mb + j, M, v - nb1, g, K2);
+                if constexpr (RAG) load_a_rag<AF32, Sync::kCoherent>(af[p][mb], v < nb1 ? A : A2, v < nb1 ? lda : lda2, 16 * mb + j, M, v < nb1 ? v : v - nb1, g, v < nb1 ? K : K2);
+                else if (v < nb1) load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A, lda, 16 * mb + j, M, v, g, K);
+                else load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A2, lda2, 16 * mb + j, M, v - nb1, g, K2);
             }
         }
     }
@@ -360,20 +371,19 @@ __device__ __forceinline__ void mma_range2(f32x4_t (&acc1)[MB][CPL], f32x4_t (&a
         for (int p = 0; p < PF; ++p) {
             const int v = blk + NW * p;
             if (v < nv) {
-                if constexpr (RAG) {
-                    if (v < nb1) fix_w_rag<CPL>(wf[p], N, v, g, col, avail);
-                    else         fix_w_rag<CPL>(wf[p], N, v - nb1, g, col, avail2);
-                }
+                if constexpr (RAG) fix_w_rag<CPL>(wf[p], N, v < nb1 ? v : v - nb1, g, col, v < nb1 ? avail : avail2);
                 if (v < nb1) mma_block<MB, CPL, AF32, RAG>(acc1, wf[p], af[p]);
                 else         mma_block<MB, CPL, AF32, RAG>(acc2, wf[p], af[p]);
                 const int nx = v + NW * PF;
                 if (nx < nv) {
-                    if (nx < nb1) load_w_block<CPL, RAG>(wf[p], W, N, nx, g, col, avail);
-                    else          load_w_block<CPL, RAG>(wf[p], W2, N, nx - nb1, g, col, avail2);
+                    if constexpr (RAG) load_w_rag<CPL>(wf[p], nx < nb1 ? W : W2, N, nx < nb1 ? nx : nx - nb1, g, col, nx < nb1 ? avail : avail2);
+                    else if (nx < nb1) load_w_block<CPL, RAG>(wf[p], W, N, nx, g, col, avail);
+                    else load_w_block<CPL, RAG>(wf[p], W2, N, nx - nb1, g, col, avail2);
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb) {
-                        if (nx < nb1) load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A, lda, 16 * mb + j, M, nx, g, K);
-                        else          load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A2, lda2, 16 * mb + j, M, nx - nb1, g, K2);
+                        if constexpr (RAG) load_a_rag<AF32, Sync::kCoherent>(af[p][mb], nx < nb1 ? A : A2, nx < nb1 ? lda : lda2, 16 * mb + j, M, nx < nb1 ? nx : nx - nb1, g, nx < nb1 ? K : K2);
+                        else if (nx < nb1) load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A, lda, 16 * mb + j, M, nx, g, K);
+                        else load_a_block<AF32, Sync::kCoherent, RAG>(af[p][mb], A2, lda2, 16 * mb + j, M, nx - nb1, g, K2);
                     }
                 }
             }
@@ -417,7 +427,10 @@ __device__ __forceinline__ void decode_tile(const DProb& P, int M, int lt, float
     constexpr int NMAT = (EPI == EPI_GATEUP) ? 2 : 1;
     constexpr int NC = 16 * CPL;
     constexpr int Q = CPL / 4;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    int lane = tid & 63;
+    if constexpr (RAG) asm volatile("" : "+v"(lane));     // (the addresses of the rows' ends are formed per tile, not held in registers across all tiles)
+    const int j = lane & 15, g = lane >> 4;
     const int tn = lt % P.tiles_n, tk = lt / P.tiles_n;
     const int n0 = tn * NC;
 

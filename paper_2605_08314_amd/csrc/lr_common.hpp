@@ -25,6 +25,16 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
     return (bf16_t)(u >> 16);
 }
 
+// An fp32 value is three bf16 parts of eight significant bits each: its upper half, the upper half of the rest, the rest of that
+// (cut off and not rounded, so that no part of a finite value is infinite; an infinity has NaN for a rest).  This takes the next
+// part of two values, as a pair, and leaves their rests.
+__device__ __forceinline__ uint32_t bf16_part(float& x, float& y) {
+    const uint32_t bx = __float_as_uint(x), by = __float_as_uint(y);
+    x -= __uint_as_float(bx & 0xffff0000u);
+    y -= __uint_as_float(by & 0xffff0000u);
+    return __builtin_amdgcn_perm(by, bx, 0x07060302u);
+}
+
 struct IoF32 {
     typedef float T;
     typedef double Acc;     // generic fp32 path accumulates in fp64 so that long reductions keep 1e-5

@@ -1,10 +1,11 @@
 """Calls whose sizes are any whole numbers or whose operands sit at any element alignment, against the fp64 oracle.
 
-The bf16 calls keep the rank-space and hidden rows in fp32 between the stages (as bf16 pairs inside the matrix cores), so the
-only coarse rounding is the result's: half a unit in the last place of each value.  Beyond that, a pair represents its value
-to 2^-17, so a stage may be off by 2^-17 of its sum of magnitudes; with random factors that sum is below ten times the largest
-result, and no call has more than four stages: 40 * 2^-17 of the largest result (rounding the rank-space rows to bf16 once, as
-the kernels for regular sizes do, is off by several times as much).  The fp32 calls sum in fp64 and round the rank-space and
+The bf16 calls keep the rank-space and hidden rows in fp32 between the stages (as three bf16 parts inside the matrix cores, which
+hold all 24 bits), so the only coarse rounding is the result's: half a unit in the last place of each value.  Beyond that there are
+the roundings of the fp32 sums: about 2^-24 of the sum of magnitudes for each of n terms, in either direction, sqrt(n) * 2^-24
+together and 2^-18 for the longest sum here; with random factors the sum of magnitudes is below ten times the largest result, and no
+call has more than four stages: 40 * 2^-18 of the largest result, and twice that as the bound (rounding the rank-space rows to
+bf16 once, as the kernels for regular sizes do, is off by several times as much).  The fp32 calls sum in fp64 and round the rank-space and
 hidden rows to fp32: the same with 2^-24."""
 import numpy as np
 import pytest
@@ -228,3 +229,52 @@ def test_infinite_weights_of_an_mlp(G, oracle, M, where, shared):
     assert inf.any()
     if ok.any():
         assert beyond_rounding(got[ok], want[ok]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("shared", [0, 1])
+@pytest.mark.parametrize("M", [1, 16, 32, 33, 150])
+def test_rank_space_and_hidden_rows_keep_all_bits(G, M, shared):
+    """Rank-space and hidden values of 21 bits whose difference is one unit in their last place: it comes out exactly wherever the next
+    factor subtracts them, so no bit of an fp32 value may be lost on the way into the matrix cores (two bf16 parts hold 16)."""
+    B = G.B
+    B.lowrank_configure(B.LR_CFG_DEVICE_SHARED, shared)
+    try:
+        # t[5], t[66] = 2^20 + 2^10 + 1 and 2^20 + 2^10
+        d, r, n = 75, 67, 131
+        x, U, V = np.zeros((M, d)), np.zeros((d, r)), np.zeros((r, n))
+        s = 2.0 ** (np.arange(M) % 5)[:, None]
+        x[:, [3, 40, 74]] = s
+        U[[3, 40, 74], 5] = 2.0 ** 20, 2.0 ** 10, 1.0
+        U[[3, 40], 66] = 2.0 ** 20, 2.0 ** 10
+        V[5, 64:], V[66, 64:] = 1.0, -1.0
+        V[5, :64], V[66, :64] = -1.0, 1.0
+        y = G.host64(G.run_linear(synth.to_dtype(x, "bf16"), synth.to_dtype(U, "bf16"), synth.to_dtype(V, "bf16"), None, "auto", "bf16"))
+        assert np.array_equal(y, s * np.where(np.arange(n) < 64, -1.0, 1.0))
+        # the same in the packed MLP: g = 64 everywhere (SiLU(64) = 64 in fp32), u = the two values in hidden columns 1 and 99, their
+        # difference in column 50; ranks 0, 20, 34 of the down factor take up each, column 0 of the result subtracts hidden rows,
+        # column 1 takes the difference that gate/up made, column 2 subtracts down-factor ranks
+        f, r_g, r_u, r_d = 101, 33, 37, 35
+        U_gu, V_g, V_u, U_d, V_d = np.zeros((d, r_g + r_u)), np.zeros((r_g, f)), np.zeros((r_u, f)), np.zeros((f, r_d)), np.zeros((r_d, d))
+        x[:, [3, 40, 74]] = 1.0
+        x[:, 10] = 1.0
+        U_gu[10, 32] = 64.0
+        V_g[32] = 1.0
+        U_gu[[3, 40, 74], r_g + 2] = 2.0 ** 20, 2.0 ** 10, 1.0
+        U_gu[[3, 40], r_g + 36] = 2.0 ** 20, 2.0 ** 10
+        V_u[2, 1] = V_u[36, 99] = V_u[2, 50] = 1.0
+        V_u[36, 50] = -1.0
+        U_d[1, 0], U_d[99, 0] = 1.0, -1.0
+        U_d[50, 10] = 1.0
+        U_d[1, 20], U_d[99, 34] = 1.0, 1.0
+        V_d[0, 0] = V_d[10, 1] = V_d[20, 74] = 1.0
+        V_d[34, 74] = -1.0
+        w = [G.dev(synth.to_dtype(a, "bf16")) for a in (x, U_gu, V_g, V_u, U_d, V_d)]
+        out = torch.full((M, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ws = B.new_workspace(B.LR_OP_PACKED_MLP, M, d, r_g + r_u + r_d, f, B.LR_BF16)
+        B.lowrank_packed_mlp(*w, None, None, None, out, "auto", ws)
+        B.lowrank_workspace_status(ws)
+        want = np.zeros((M, d))
+        want[:, [0, 1, 74]] = 64.0
+        assert np.array_equal(G.host64(out), want)
+    finally:
+        B.lowrank_configure(B.LR_CFG_DEVICE_SHARED, 0)
