@@ -152,6 +152,10 @@ int lowrank_workspace_status(const void* workspace, void* stream) {
         set_error("a device-side wait between stages gave up; the results of that call are NaN and the workspace must be prepared again (lowrank_workspace_init)");
         return LR_ERR_LAUNCH;
     }
+    if (c.magic == kCtrlFailed || c.magic == kCtrlBusy || c.magic == kCtrlFill) {
+        set_error("the preparation of the workspace gave up or was cut off; the results of that call are NaN and the workspace must be prepared again (lowrank_workspace_init)");
+        return LR_ERR_LAUNCH;
+    }
     return LR_OK;
 }
 

@@ -33,13 +33,17 @@ typedef DStageT<kMaxProb> DStage;
 // `magic` says whether the block is valid.  A workspace may arrive with any contents (fresh allocation): the first
 // kernel that needs the block and does not find kCtrlReady there prepares it itself (one wave wins a compare-and-swap
 // to kCtrlBusy, zeroes the block and the shared-K flags and publishes kCtrlFill; every wave of the launch then
-// zeroes its share of the accumulator areas, and the last one done publishes kCtrlReady), so no host-side initialisation is required and a graph replay never depends on one.
+// zeroes its share of the accumulator areas, and the last one done publishes kCtrlReady), so no host-side initialisation is
+// required and a graph replay never depends on one.  Every step is a compare-and-swap from the word before it.  A wave whose wait
+// for the next word gives up puts kCtrlFailed in its place, which nothing but a new preparation replaces: a launch therefore
+// leaves kCtrlReady or kCtrlFailed behind, never a preparation half done for the next call to go on with.
 constexpr int kBarriers = 3;
 constexpr int kSlots = 16;
 constexpr int kSlotStride = 32;   // uint32 words between slots (128 bytes)
 constexpr uint64_t kCtrlReady = 0x6c72776b73703031ull;
 constexpr uint64_t kCtrlBusy = 0x6c72776b73703030ull;
 constexpr uint64_t kCtrlFill = 0x6c72776b73703032ull;
+constexpr uint64_t kCtrlFailed = 0x6c72776b73703033ull;
 struct Ctrl {
     uint64_t magic;                     // kCtrlReady: everything below and the accumulator areas are in their between-calls state
     uint32_t epoch;                     // number of fused calls completed on this workspace

@@ -666,16 +666,27 @@ __device__ __forceinline__ CtrlLoads ctrl_issue(const Ctrl* c) {
     return L;
 }
 
-constexpr uint32_t kPrepareSpinLimit = 1u << 24;
-
-// wait until the control block's word is kCtrlReady, or with `or_fill` kCtrlFill; true when it is kCtrlFill
-__device__ __forceinline__ bool ctrl_wait(Ctrl* c, bool or_fill, bool& ok) {
+__device__ __forceinline__ uint64_t ctrl_word(const Ctrl* c) {                // wave-uniform
+    const uint64_t v = ld_agent64(&c->magic);
+    return (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)v) | ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32);
+}
+// by one lane of the wave, wave-uniform result
+__device__ __forceinline__ bool ctrl_swap(Ctrl* c, uint64_t from, uint64_t to) {
+    uint32_t won = 0;
+    if ((threadIdx.x & 63) == 0) {
+        uint64_t expect = from;
+        won = __hip_atomic_compare_exchange_strong(&c->magic, &expect, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
+    }
+    return __builtin_amdgcn_readfirstlane(won) != 0u;
+}
+// Wait until the control block's word is kCtrlReady, or with `or_fill` kCtrlFill; returns it, or kCtrlFailed.  After `limit` polls
+// the word is replaced by kCtrlFailed; where that fails it has moved on, which it does twice at most.
+__device__ __forceinline__ uint64_t ctrl_wait(Ctrl* c, bool or_fill, uint32_t limit) {
     uint32_t spins = 0;
     for (;;) {
-        const uint64_t v = ld_agent64(&c->magic);
-        const uint32_t fill = __builtin_amdgcn_readfirstlane((uint32_t)(v == kCtrlFill));
-        if (__builtin_amdgcn_readfirstlane((uint32_t)(v == kCtrlReady)) != 0u || (or_fill && fill != 0u)) return fill != 0u;
-        if (++spins > kPrepareSpinLimit) { ok = false; return false; }
+        const uint64_t v = ctrl_word(c);
+        if (v == kCtrlReady || v == kCtrlFailed || (or_fill && v == kCtrlFill)) return v;
+        if (++spins > limit && ctrl_swap(c, v, kCtrlFailed)) return kCtrlFailed;
         __builtin_amdgcn_s_sleep(8);
     }
 }
@@ -683,42 +694,37 @@ __device__ __forceinline__ bool ctrl_wait(Ctrl* c, bool or_fill, bool& ok) {
 // First call on a workspace that nobody prepared: one wave of the whole launch wins the right to zero the control block, then
 // every wave zeroes its share of the accumulator areas (each wave of a fused launch comes here exactly once: none can see
 // kCtrlReady before all have).  Device-coherent stores, so that no cache has to be written back.  (One wave zeroing all 8 MiB
-// took 265 us of such a call's 278.)  Wave-uniform; returns false if a wait gave up.
-__device__ __noinline__ bool ctrl_prepare(Ctrl* c, char* acc0, size_t acc_bytes, uint64_t observed) {
+// took 265 us of such a call's 278.)  Wave-uniform; returns false if a wait gave up, here or in another wave of this launch or an
+// earlier one.  Like every wait of a fused launch these need all of its workgroups resident, and like them they end after `limit` polls.
+__device__ __noinline__ bool ctrl_prepare(Ctrl* c, char* acc0, size_t acc_bytes, uint64_t observed, uint32_t limit) {
     const uint32_t lane = threadIdx.x & 63;
-    uint32_t won = 0;
-    if (lane == 0 && observed != kCtrlBusy && observed != kCtrlFill) {
-        uint64_t expect = observed;
-        won = __hip_atomic_compare_exchange_strong(&c->magic, &expect, kCtrlBusy, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
-    }
-    won = __builtin_amdgcn_readfirstlane(won);
-    if (won) {
+    if (observed != kCtrlBusy && observed != kCtrlFill && observed != kCtrlFailed && ctrl_swap(c, observed, kCtrlBusy)) {
         // header behind the magic word + shared-K flags (contiguous)
         char* h = reinterpret_cast<char*>(c) + 8;
         const uint32_t n8 = (uint32_t)((kHeaderBytes + kSkFlagBytes) / 8 - 1);
         for (uint32_t i = lane; i < n8; i += 64) st_coherent_b64(h + 8 * i, make_uint2(0u, 0u));
         drain_memory();
-        if (lane == 0) __hip_atomic_store(&c->magic, kCtrlFill, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ctrl_swap(c, kCtrlBusy, kCtrlFill);
     }
-    bool ok = true;
-    if (ctrl_wait(c, true, ok)) {
+    uint64_t word = ctrl_wait(c, true, limit);
+    if (word == kCtrlFill) {
         const uint32_t n8 = (uint32_t)(2 * acc_bytes / 8), threads = gridDim.x * blockDim.x;
         for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n8; i += threads) st_coherent_b64(acc0 + 8 * (size_t)i, make_uint2(0u, 0u));
         drain_memory();
-        if (lane == 0 && __hip_atomic_fetch_add(&c->prep_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == threads / 64u - 1u)
-            __hip_atomic_store(&c->magic, kCtrlReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ctrl_wait(c, false, ok);
+        uint32_t before = 0;
+        if (lane == 0) before = __hip_atomic_fetch_add(&c->prep_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane(before) == threads / 64u - 1u) ctrl_swap(c, kCtrlFill, kCtrlReady);
+        word = ctrl_wait(c, false, limit);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return ok;
+    return word == kCtrlReady;
 }
 
 // Wave-uniform.  `bad` (LDS word of the workgroup) is raised when the workspace carries an earlier failure.
-__device__ __forceinline__ CtrlSnap ctrl_resolve(Ctrl* ctrl, char* acc0, size_t acc_bytes, CtrlLoads L, uint32_t* bad) {
+__device__ __forceinline__ CtrlSnap ctrl_resolve(Ctrl* ctrl, char* acc0, size_t acc_bytes, CtrlLoads L, uint32_t* bad, uint32_t limit) {
     const uint64_t magic = (uint64_t)L.m.x | ((uint64_t)L.m.y << 32);
     if (__builtin_amdgcn_readfirstlane((uint32_t)(magic != kCtrlReady)) != 0u) {
-        const bool ok = ctrl_prepare(ctrl, acc0, acc_bytes, magic);
+        const bool ok = ctrl_prepare(ctrl, acc0, acc_bytes, magic, limit);
         L = ctrl_issue(ctrl);
         if (!ok) {
             if ((threadIdx.x & 63) == 0) { __hip_atomic_store(&ctrl->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); *bad = 1u; }
@@ -738,10 +744,11 @@ struct CtrlGate {
     Ctrl* ctrl; char* acc0; size_t acc_bytes;       // by value: taking the address of a kernel argument would force a private copy of all of them
     const CtrlLoads* loads; CtrlSnap* snap; size_t* shift;
     uint32_t* bad;
+    uint32_t limit;
     __device__ __forceinline__ void operator()(uint32_t&) const {}
     __device__ __forceinline__ void before_epilogue() const { (*this)(); }
     __device__ __forceinline__ void operator()() const {
-        *snap = ctrl_resolve(ctrl, acc0, acc_bytes, *loads, bad);
+        *snap = ctrl_resolve(ctrl, acc0, acc_bytes, *loads, bad, limit);
         *shift = (size_t)snap->p * acc_bytes;
     }
 };
@@ -818,7 +825,8 @@ struct GridWaitPlain : GridWait {
 // Clear what the previous call left in the other accumulator area and the other parity's barrier
 // counters (nobody uses them during this call).  Called by every workgroup before its first arrive.
 __device__ __forceinline__ void fused_clear_other(const FusedCommon& fc, const CtrlSnap& c) {
-    const uint32_t n4 = (c.dirty_other + 3u) >> 2;
+    // (where the preparation gave up nobody vouches for the extent)
+    const uint32_t dirty4 = (c.dirty_other + 3u) >> 2, most4 = (uint32_t)(fc.acc_bytes / 16), n4 = dirty4 < most4 ? dirty4 : most4;
     float4* other = reinterpret_cast<float4*>(fc.acc0 + (size_t)(1u - c.p) * fc.acc_bytes);
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += gridDim.x * blockDim.x)
         other[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -866,7 +874,7 @@ __global__ void __launch_bounds__(64 * NW) k_decode_fused2(Fused2Args<NP> fa) {
     __syncthreads();
     CtrlSnap cs;
     size_t shift = 0;
-    const CtrlGate gate = {fa.fc.ctrl, fa.fc.acc0, fa.fc.acc_bytes, &cl, &cs, &shift, &s_bad};
+    const CtrlGate gate = {fa.fc.ctrl, fa.fc.acc0, fa.fc.acc_bytes, &cl, &cs, &shift, &s_bad, fa.fc.spin_limit};
     bool resolved = false;
     LR_STAMP(0);
     for (int tile = blockIdx.x; tile < fa.s1.total_tiles; tile += gridDim.x) {
@@ -910,7 +918,7 @@ __global__ void __launch_bounds__(64 * NW) k_decode_fused_mlp(FusedMlpArgs fa) {
     __syncthreads();
     CtrlSnap cs;
     size_t shift = 0;
-    const CtrlGate gate = {fa.fc.ctrl, fa.fc.acc0, fa.fc.acc_bytes, &cl, &cs, &shift, &s_bad};
+    const CtrlGate gate = {fa.fc.ctrl, fa.fc.acc0, fa.fc.acc_bytes, &cl, &cs, &shift, &s_bad, fa.fc.spin_limit};
     const uint32_t G = gridDim.x;
     LR_STAMP(0);
     // A: t_gu += x U_gu

@@ -166,9 +166,11 @@ int generic_pack_panels(const void* W, int64_t K, int64_t N, void* panels, hipSt
 // that shares K, lowrank_workspace_init): ONE small launch.  When the control block carries the ready word (every call but
 // the first) the single workgroup leaves at once; otherwise it zeroes the control block, the flags and the accumulator areas
 // (8 MiB by 1024 threads: some tens of microseconds, once) and then writes the word.  Nothing is copied back, nothing waits.
+// A preparation that gave up earlier is done over, and the error word keeps the failure (lowrank_workspace_init zeroes the word first).
 __global__ void __launch_bounds__(1024) k_ws_prepare(char* ws) {
     Ctrl* c = reinterpret_cast<Ctrl*>(ws);
-    if (__hip_atomic_load(&c->magic, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kCtrlReady) return;
+    const uint64_t word = __hip_atomic_load(&c->magic, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (word == kCtrlReady) return;
     uint2* head = reinterpret_cast<uint2*>(ws) + 1;                               // behind the magic word
     const size_t n_head = (kHeaderBytes + kSkFlagBytes) / 8 - 1;
     uint4* acc = reinterpret_cast<uint4*>(ws + kHeaderBytes + kSkFlagBytes + kDecPartBytes);
@@ -177,7 +179,10 @@ __global__ void __launch_bounds__(1024) k_ws_prepare(char* ws) {
     for (size_t i = threadIdx.x; i < n_acc; i += 1024) acc[i] = make_uint4(0u, 0u, 0u, 0u);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");                             // the zeroes are in memory before the word says so
     __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(&c->magic, kCtrlReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) {
+        if (word == kCtrlFailed) __hip_atomic_store(&c->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&c->magic, kCtrlReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 int ws_prepare(void* ws, hipStream_t s) {

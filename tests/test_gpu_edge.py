@@ -518,6 +518,64 @@ def test_wait_that_gives_up_poisons_results_and_is_reported(G, oracle):
     B.lowrank_workspace_status(ws)
 
 
+def test_preparation_that_gives_up_is_a_failure_until_prepared_again(G, oracle):
+    """The first call on an unprepared workspace with a limit of zero polls: whoever does not find the preparation complete at its first
+    look gives it up.  No plausible numbers then or in any later decode call, the status call reports it, also after a prefill
+    product that keeps state in the same workspace, and preparing the workspace again restores normal service."""
+    B = G.B
+    args, want_fn = _mlp_case(4, 985)
+    dev = [G.dev(a) for a in args]
+    want = want_fn(oracle)
+    M, K, N = 4096, 8192, 1536
+    assert B.lowrank_prefill_tile(M, K, N, 1)[2] == 1            # workgroups hand partial sums to each other through the workspace
+    g = torch.Generator(device="cuda"); g.manual_seed(1)
+    x, U = (torch.randn(s, device="cuda", dtype=torch.bfloat16, generator=g) for s in ((M, K), (K, N)))
+    ws = torch.empty(B.lowrank_workspace_bytes(B.LR_OP_LINEAR, M, K, N, 0, B.LR_BF16, "auto"), dtype=torch.uint8, device="cuda")
+    ws.fill_(255)
+
+    def call():
+        out = torch.zeros((4, 1024), dtype=torch.bfloat16, device="cuda")
+        B.lowrank_packed_mlp(*dev, None, None, None, out, "decode", ws)
+        torch.cuda.synchronize()
+        return G.host64(out)
+
+    B.lowrank_configure(B.LR_CFG_WAIT_LIMIT, 0)
+    try:
+        got = call()
+    finally:
+        B.lowrank_configure(B.LR_CFG_WAIT_LIMIT, 1 << 20)
+    assert np.isnan(got).any()
+    for _ in range(2):
+        with pytest.raises(B.LowrankError) as e:
+            B.lowrank_workspace_status(ws)
+        assert e.value.status == -7
+        assert np.isnan(call()).all()
+        t = torch.empty((M, N), device="cuda", dtype=torch.bfloat16)
+        B.lowrank_rank_project(x, U, t, ws)
+    assert max_rel_err(G.host64(t[:100]), x[:100].double().cpu().numpy() @ U.double().cpu().numpy()) <= TOL["bf16"]
+    B.lowrank_workspace_init(ws)
+    assert max_rel_err(call(), want) <= TOL["bf16"]
+    B.lowrank_workspace_status(ws)
+
+
+@pytest.mark.parametrize("word", [0x6c72776b73703030, 0x6c72776b73703032, 0x6c72776b73703033], ids=["busy", "fill", "failed"])
+def test_status_of_a_preparation_cut_off(G, oracle, word):
+    """A control block that was left in the middle of its preparation is no valid one: reported until it is prepared again."""
+    B = G.B
+    args, want_fn = _mlp_case(4, 986)
+    ws = B.new_workspace(B.LR_OP_PACKED_MLP, 4, 1024, 576, 2816, B.LR_BF16)
+    ws[:8] = torch.from_numpy(np.array([word], dtype=np.uint64).view(np.uint8).copy()).cuda()
+    with pytest.raises(B.LowrankError) as e:
+        B.lowrank_workspace_status(ws)
+    assert e.value.status == -7
+    B.lowrank_workspace_init(ws)
+    B.lowrank_workspace_status(ws)
+    out = torch.zeros((4, 1024), dtype=torch.bfloat16, device="cuda")
+    B.lowrank_packed_mlp(*[G.dev(a) for a in args], None, None, None, out, "decode", ws)
+    B.lowrank_workspace_status(ws)
+    assert max_rel_err(G.host64(out), want_fn(oracle)) <= TOL["bf16"]
+
+
 # ------------------------------------------------------------------ exact arithmetic: indexing errors cannot hide under a tolerance
 def _sparse_int(rng, shape, nnz_axis, nnz):
     """Matrix of -1 / 0 / +1 with exactly `nnz` nonzeros along `nnz_axis` of every slice."""
