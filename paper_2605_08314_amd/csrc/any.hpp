@@ -22,7 +22,10 @@ struct AnyProb {
     int splits, kchunk; int64_t split_stride;                  // ANY_T: K chunks, rows per chunk, floats between the chunks' results
     int tiles_n, tile_begin;
 };
-struct AnyArgs { AnyProb p[kMaxAny]; int nprob, M, tiles_m, total; };
+struct AnyArgs { AnyProb p[kMaxAny]; int nprob, M, tiles_m, first, count; };      // a launch takes tiles [first, first + count)
+// Tiles of a launch: a grid has fewer than 2^32 threads and a workgroup up to 512.  More tiles (2^27 rows of a narrow fp32 result)
+// run as several launches.
+constexpr int kAnyLaunchTiles = 1 << 22;
 
 // Rows, K and N the kernels index with 32-bit numbers
 bool any_rows_ok(int64_t M);

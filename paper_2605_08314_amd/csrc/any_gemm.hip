@@ -241,9 +241,10 @@ __global__ void __launch_bounds__(256, 2) k_any_gemm(AnyArgs ga) {
     char* ring = reinterpret_cast<char*>(lds);
     char* patch = ring + wave * 4096;                              // (the products leave the ring through a barrier)
     // workgroups go to the 8 XCDs round-robin: give each XCD a contiguous run of tiles
-    const int per = (ga.total + 7) >> 3;
-    const int id = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if (id >= ga.total) return;
+    const int per = (ga.count + 7) >> 3;
+    const int local = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (local >= ga.count) return;
+    const int id = ga.first + local;
     int pi = 0;
 #pragma unroll
     for (int i = 1; i < kMaxAny; ++i)
@@ -375,15 +376,20 @@ int any_launch_bf16(AnyArgs& a, bool a_f32, int epi, hipStream_t s) {
         total += (int64_t)a.tiles_m * p.tiles_n * p.splits;
     }
     if (total <= 0) return LR_OK;
-    if (total >= (1ll << 28)) { set_error("too many output tiles for one launch"); return LR_ERR_UNSUPPORTED; }
-    a.total = (int)total;
-    const dim3 grid((unsigned)(((total + 7) / 8) * 8)), block(256);
-    if (epi == ANY_T) {
-        if (a_f32) hipLaunchKernelGGL((k_any_gemm<true, ANY_T>), grid, block, 0, s, a);
-        else       hipLaunchKernelGGL((k_any_gemm<false, ANY_T>), grid, block, 0, s, a);
-    } else if (epi == ANY_GATEUP) hipLaunchKernelGGL((k_any_gemm<true, ANY_GATEUP>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_any_gemm<true, ANY_OUT>), grid, block, 0, s, a);
-    return launch_status("product of any sizes");
+    if (total >= (1ll << 31)) { set_error("too many output tiles"); return LR_ERR_UNSUPPORTED; }
+    for (int64_t first = 0; first < total; first += kAnyLaunchTiles) {
+        a.first = (int)first;
+        a.count = (int)(total - first < kAnyLaunchTiles ? total - first : kAnyLaunchTiles);
+        const dim3 grid((unsigned)((a.count + 7) / 8 * 8)), block(256);
+        if (epi == ANY_T) {
+            if (a_f32) hipLaunchKernelGGL((k_any_gemm<true, ANY_T>), grid, block, 0, s, a);
+            else       hipLaunchKernelGGL((k_any_gemm<false, ANY_T>), grid, block, 0, s, a);
+        } else if (epi == ANY_GATEUP) hipLaunchKernelGGL((k_any_gemm<true, ANY_GATEUP>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_any_gemm<true, ANY_OUT>), grid, block, 0, s, a);
+        const int st = launch_status("product of any sizes");
+        if (st != LR_OK) return st;
+    }
+    return LR_OK;
 }
 
 int any_reduce(const float* part, float* dst, int64_t n, int splits, int64_t stride, hipStream_t s) {

@@ -113,9 +113,10 @@ __global__ void __launch_bounds__(512, MB == 1 ? 4 : 2) k_f32_gemm(AnyArgs ga) {
     const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroups go to the 8 XCDs round-robin: each XCD gets a run of tiles, row tiles of one column tile next to each other
-    const int per = (ga.total + 7) >> 3;
-    const int id = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if (id >= ga.total) return;
+    const int per = (ga.count + 7) >> 3;
+    const int local = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (local >= ga.count) return;
+    const int id = ga.first + local;
     int pi = 0;
 #pragma unroll
     for (int i = 1; i < kMaxAny; ++i)
@@ -198,14 +199,19 @@ static int launch_f32(AnyArgs& a, int epi, hipStream_t s) {
         total += (int64_t)a.tiles_m * p.tiles_n;
     }
     if (total <= 0) return LR_OK;
-    if (total >= (1ll << 28)) { set_error("too many output tiles for one launch"); return LR_ERR_UNSUPPORTED; }
-    a.total = (int)total;
-    const dim3 grid((unsigned)(((total + 7) / 8) * 8)), block(512);
-    if (epi == ANY_T) hipLaunchKernelGGL((k_f32_gemm<MB, CPL, ANY_T>), grid, block, 0, s, a);
-    else if (epi == ANY_GATEUP) {
-        if constexpr (MB == 1) hipLaunchKernelGGL((k_f32_gemm<MB, CPL, ANY_GATEUP>), grid, block, 0, s, a);
-    } else hipLaunchKernelGGL((k_f32_gemm<MB, CPL, ANY_OUT>), grid, block, 0, s, a);
-    return launch_status("fp32 product");
+    if (total >= (1ll << 31)) { set_error("too many output tiles"); return LR_ERR_UNSUPPORTED; }
+    for (int64_t first = 0; first < total; first += kAnyLaunchTiles) {
+        a.first = (int)first;
+        a.count = (int)(total - first < kAnyLaunchTiles ? total - first : kAnyLaunchTiles);
+        const dim3 grid((unsigned)((a.count + 7) / 8 * 8)), block(512);
+        if (epi == ANY_T) hipLaunchKernelGGL((k_f32_gemm<MB, CPL, ANY_T>), grid, block, 0, s, a);
+        else if (epi == ANY_GATEUP) {
+            if constexpr (MB == 1) hipLaunchKernelGGL((k_f32_gemm<MB, CPL, ANY_GATEUP>), grid, block, 0, s, a);
+        } else hipLaunchKernelGGL((k_f32_gemm<MB, CPL, ANY_OUT>), grid, block, 0, s, a);
+        const int st = launch_status("fp32 product");
+        if (st != LR_OK) return st;
+    }
+    return LR_OK;
 }
 
 int any_launch_f32(AnyArgs& a, int epi, hipStream_t s) {

@@ -278,3 +278,29 @@ def test_rank_space_and_hidden_rows_keep_all_bits(G, M, shared):
         assert np.array_equal(G.host64(out), want)
     finally:
         B.lowrank_configure(B.LR_CFG_DEVICE_SHARED, 0)
+
+
+@pytest.mark.parametrize("kind", ["linear_f32", "mlp_f32", "qkv_bf16"])
+def test_more_tiles_than_one_launch_has(G, kind):
+    """Hundreds of millions of rows of one column: more workgroups than a grid may have (2^32 threads)."""
+    B = G.B
+    M = (1 << (27 if kind == "mlp_f32" else 28)) + 40
+    g = torch.Generator(device="cuda"); g.manual_seed(3)
+    x = torch.randn((M, 1), device="cuda", dtype=torch.bfloat16 if kind == "qkv_bf16" else torch.float32, generator=g)
+    w = lambda *s: torch.randn(s, device="cuda", dtype=x.dtype, generator=g)     # noqa: E731
+    if kind == "linear_f32":
+        U, V, y = w(1, 1), w(1, 1), torch.full_like(x, float("nan"))
+        B.lowrank_linear(x, U, V, None, y, "auto", B.new_workspace(B.LR_OP_LINEAR, M, 1, 1, 1, B.LR_F32))
+        assert torch.equal(y, x * U * V)                                          # products of one term: two fp32 roundings on either side
+    elif kind == "mlp_f32":
+        U_gu, V_g, V_u, U_d, V_d = w(1, 2), w(1, 1), w(1, 1), w(1, 1), w(1, 1)
+        y = torch.full_like(x, float("nan"))
+        B.lowrank_packed_mlp(x, U_gu, V_g, V_u, U_d, V_d, None, None, None, y, "auto", B.new_workspace(B.LR_OP_PACKED_MLP, M, 1, 3, 1, B.LR_F32))
+        h = torch.nn.functional.silu(x * U_gu[0, 0] * V_g) * (x * U_gu[0, 1] * V_u)
+        torch.testing.assert_close(y, h * U_d * V_d, rtol=40 * 8 * 2.0 ** -24, atol=1e-30)      # (as for the packed MLP above)
+    else:
+        U, V = [w(1, 1) for _ in range(8)], [w(1, 1) for _ in range(8)]
+        y = [torch.full_like(x, float("nan")) for _ in range(8)]
+        B.lowrank_qkv(x, U, V, None, y, None, "auto", B.new_workspace(B.LR_OP_QKV, M, 1, 8, 8, B.LR_BF16))
+        for i in range(8):                                                        # 24-bit products: exact before the one rounding
+            assert torch.equal(y[i], (x.float() * U[i].float() * V[i].float()).to(torch.bfloat16)), i
