@@ -29,10 +29,10 @@ template <bool AF32> struct AnyRegs { uint4 a[AF32 ? 4 : 2]; uint4 b[2]; };
 
 struct AnyOperands {
     const char* a[2];            // this thread's A rows at k = 0 of its units
-    const bf16_t* B;             // tile column n0 of row 0
-    int N, n0, kend;             // kend: end of the K range
+    const bf16_t* B;             // the tile's first column of row 0
+    int N;
     int64_t avail;               // elements of B from `B` to the matrix's end
-    int K;
+    int K;                       // end of the K range
 };
 
 template <bool AF32>
@@ -147,7 +147,7 @@ __device__ __forceinline__ void any_product(f32x16_t (&acc)[2][2], const void* A
     const int ns = (kend - kbeg + ABK - 1) / ABK;
     if (ns <= 0) return;
     AnyOperands o;
-    o.B = B + n0; o.N = N; o.n0 = n0; o.kend = kend; o.K = kend; o.avail = (int64_t)K * N - n0;
+    o.B = B + n0; o.N = N; o.K = kend; o.avail = (int64_t)K * N - n0;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         int m = m0 + j * 64 + (tid >> 2);

@@ -103,10 +103,10 @@ struct FusedCommon {
 template <int NP> struct Fused2Args { FusedCommon fc; DStageT<NP> s1, s2; };
 struct FusedMlpArgs { FusedCommon fc; DStageT<1> a, b, c, d; };
 
-// Fused launches (all stages in one kernel, `grid` resident workgroups of 8 waves).  cpl* = columns per lane
-// of each stage.  Return LR_ERR_UNSUPPORTED if the grid would not be fully resident.
-int decode_launch_fused2(const FusedCommon& fc, const DStage& s1, const DStage& s2, int cpl1, int cpl2, int grid, hipStream_t s);
-int decode_launch_fused_mlp(const FusedMlpArgs& fa, int cpl_a, int cpl_c, int cpl_d, int grid, hipStream_t s);
+// Fused launches (all stages in one kernel, `grid` resident workgroups of 8 waves).  Return LR_ERR_LAUNCH
+// if the grid would not be fully resident.
+int decode_launch_fused2(const FusedCommon& fc, const DStage& s1, const DStage& s2, int grid, hipStream_t s);
+int decode_launch_fused_mlp(const FusedMlpArgs& fa, int grid, hipStream_t s);
 // The same for whole-number sizes and any alignment (the RAG kernels, decode_ragged.hip)
 int decode_launch_fused2_rag(const FusedCommon& fc, const DStage& s1, const DStage& s2, int grid, hipStream_t s);
 int decode_launch_fused_mlp_rag(const FusedMlpArgs& fa, int grid, hipStream_t s);
@@ -119,9 +119,9 @@ extern bool g_device_shared;        // other work may occupy CUs: no launch may 
 extern uint32_t g_wait_limit;       // polls after which a device-side wait gives up
 int ws_prepare(void* ws, hipStream_t s);   // enqueue the check-and-prepare launches (calls that run no fused decode kernel)
 
-// Launch one stage: cpl = bf16 columns per lane (4 or 8), a_f32 = activations are fp32 (rank-space
+// Launch one stage: a_f32 = activations are fp32 (rank-space
 // accumulators) rather than bf16, epi = EPI_*.
-int decode_launch_stage(const DStage& st, int cpl, bool a_f32, int epi, hipStream_t s);
+int decode_launch_stage(const DStage& st, bool a_f32, int epi, hipStream_t s);
 
 // Host planners (decode_plan.hip).  form: how the factors are stored and which rule holds for the sizes of every product --
 // DF_ROWS and DF_PANELS (row-major, 64-column panels of lowrank_pack_panels) need decode_shape_ok(...) and 16-byte aligned

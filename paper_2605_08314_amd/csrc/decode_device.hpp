@@ -2,8 +2,7 @@
 // product C[M, N] (+)= A[M, K] * W[K, N] whose cost is streaming W from HBM exactly once.
 //
 // Work decomposition.  A workgroup (4 wavefronts of 64 lanes) owns one tile of W:
-// KS rows x NC columns (NC = 16 * CPL, CPL = bf16 columns per lane: 4 -> 8-byte loads,
-// 8 -> 16-byte loads).  Its waves take the tile's 32-row blocks round-robin.  For one block a lane
+// KS rows x NC columns (NC = 16 * CPL = 64, CPL = 4 bf16 columns per lane: 8-byte loads).  Its waves take the tile's 32-row blocks round-robin.  For one block a lane
 // (j = lane % 16, g = lane / 16) loads rows 8g..8g+7, columns CPL*j..CPL*j+CPL-1: every load
 // instruction of the wave covers four full row segments of NC*2 bytes, i.e. coalesced and
 // contiguous, straight from the row-major factor -- no repacking of U or V is needed.
@@ -28,7 +27,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x8_t __attribute__((ext_vector_type(8)));
 
-template <int CPL> struct WFrag { uint32_t w[8][CPL / 2]; };   // 8 k-rows x CPL bf16 columns
+template <int CPL> struct WFrag { static_assert(CPL == 4, "64-column tiles"); uint32_t w[8][CPL / 2]; };   // 8 k-rows x CPL bf16 columns
 // 8 consecutive k of one token row, as loaded: packed bf16 (4 dwords) or raw fp32 (8 dwords, converted
 // only when the MFMA consumes it, so that issuing the load never waits on earlier loads).
 template <bool AF32> struct AFrag { uint32_t a[AF32 ? 8 : 4]; };
@@ -47,13 +46,8 @@ __device__ __forceinline__ void load_w(WFrag<CPL>& f, const bf16_t* __restrict__
     const bf16_t* p = W + (size_t)row0 * (size_t)N + col;
 #pragma unroll
     for (int a = 0; a < 8; ++a) {
-        if constexpr (CPL == 8) {
-            const uint4 v = *reinterpret_cast<const uint4*>(p + (size_t)a * N);
-            f.w[a][0] = v.x; f.w[a][1] = v.y; f.w[a][2] = v.z; f.w[a][3] = v.w;
-        } else {
-            const uint2 v = *reinterpret_cast<const uint2*>(p + (size_t)a * N);
-            f.w[a][0] = v.x; f.w[a][1] = v.y;
-        }
+        const uint2 v = *reinterpret_cast<const uint2*>(p + (size_t)a * N);
+        f.w[a][0] = v.x; f.w[a][1] = v.y;
     }
 }
 
@@ -80,7 +74,6 @@ __device__ __forceinline__ void st_coherent_b64(void* p, uint2 v) {
 //                ranks 701 / 746 / 659.)
 template <int CPL>
 __device__ __forceinline__ void load_w_rag(WFrag<CPL>& f, const bf16_t* __restrict__ W, int N, int kb, int g, int col, int64_t avail) {
-    static_assert(CPL == 4, "64-column tiles");
     const bf16_t* base = W + (size_t)(32 * kb) * (size_t)N;                        // uniform
     const int64_t left = avail - 4 - (int64_t)(32 * kb) * N;                       // last in-bounds start of 4 elements, from there
     const int last = left < 0x7fffffff ? (int)left : 0x7fffffff;
@@ -261,9 +254,6 @@ constexpr bool kPlainActsFwd = true;
 #endif
 struct NoSync { static constexpr bool kCoherent = false, kFused = false; __device__ __forceinline__ void operator()(uint32_t&) const {}
                 __device__ __forceinline__ void before_epilogue() const {} };
-// Same, for later tiles of a stage whose input other workgroups of this launch produced.
-struct NoSyncCoherent { static constexpr bool kCoherent = true, kFused = true; __device__ __forceinline__ void operator()(uint32_t&) const {}
-                        __device__ __forceinline__ void before_epilogue() const {} };
 // Later tiles of a stage whose input (accumulators added with device-scope atomics, hidden rows written with
 // device-coherent stores) no workgroup on this XCD has read before the stage's barrier in this
 // launch: plain cached loads are safe (first touch misses L2) and let the other workgroups hit in L2.
@@ -393,19 +383,13 @@ __device__ __forceinline__ void mma_range2(f32x4_t (&acc1)[MB][CPL], f32x4_t (&a
 
 template <int CPL>
 __device__ __forceinline__ void store_bf16_row(bf16_t* dst, const float (&v)[CPL]) {
-    if constexpr (CPL == 8) {
-        uint4 o; o.x = pack2(v[0], v[1]); o.y = pack2(v[2], v[3]); o.z = pack2(v[4], v[5]); o.w = pack2(v[6], v[7]);
-        *reinterpret_cast<uint4*>(dst) = o;
-    } else {
-        uint2 o; o.x = pack2(v[0], v[1]); o.y = pack2(v[2], v[3]);
-        *reinterpret_cast<uint2*>(dst) = o;
-    }
+    uint2 o; o.x = pack2(v[0], v[1]); o.y = pack2(v[2], v[3]);
+    *reinterpret_cast<uint2*>(dst) = o;
 }
 
 // nv of CPL consecutive elements, at any 2-byte alignment
 template <int CPL>
 __device__ __forceinline__ void store_cols(bf16_t* dst, const bf16_t (&o)[CPL], int nv) {
-    static_assert(CPL == 4, "64-column tiles");
     if (nv >= CPL) __builtin_memcpy(dst, o, 2 * CPL);
     else {
 #pragma unroll
@@ -590,7 +574,7 @@ __device__ __forceinline__ void decode_tile(const DProb& P, int M, int lt, float
                 if (P.bias2) load_bf16_row<CPL>(bu, P.bias2 + n);
 #pragma unroll
                 for (int b = 0; b < CPL; ++b) hv[b] = silu_f32(val[0][b] + bg[b]) * (val[NMAT - 1][b] + bu[b]);
-                if constexpr (CPL == 4 && Sync::kFused) {   // fused launch: another workgroup reads h next
+                if constexpr (Sync::kFused) {   // fused launch: another workgroup reads h next
                     st_coherent_b64(P.Y + (size_t)m * P.N + n, make_uint2(pack2(hv[0], hv[1]), pack2(hv[2], hv[3])));
                 } else {
                     store_bf16_row<CPL>(P.Y + (size_t)m * P.N + n, hv);

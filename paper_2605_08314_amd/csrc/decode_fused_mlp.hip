@@ -13,25 +13,18 @@ namespace lr {
 // Both split-K stages add with atomics at every row count.  (Partial tiles in slots and a sum by the last K-slice to arrive were
 // 0.3 us faster from 25 rows on while their signal did not wait for the stores it announces; with that wait 33.4 us at 32 rows
 // against 33.2 with atomics.)
-template <int MB, int CA, int CC, int CD>
+template <int MB>
 static int launch_mlp(const FusedMlpArgs& fa, int grid, hipStream_t s) {
     constexpr int NW = 8;
-    void (*kern)(FusedMlpArgs) = k_decode_fused_mlp<MB, CA, CC, CD, MB == 1 ? 3 : 2, 2, 3, 3, NW>;
+    void (*kern)(FusedMlpArgs) = k_decode_fused_mlp<MB, 4, 4, 4, MB == 1 ? 3 : 2, 2, 3, 3, NW>;
     if (!decode_grid_is_resident((const void*)kern, 64 * NW, grid)) return LR_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), 0, s, fa);
     return launch_status("fused decode (packed MLP)");
 }
 
-template <int MB>
-static int launch_mlp_cpl(const FusedMlpArgs& fa, int ca, int cc, int cd, int grid, hipStream_t s) {
-    if (cd != 4 || ca != 4 || cc != 4) { set_error("bad decode tile configuration"); return LR_ERR_UNSUPPORTED; }
-    return launch_mlp<MB, 4, 4, 4>(fa, grid, s);
-}
-
-int decode_launch_fused_mlp(const FusedMlpArgs& fa, int cpl_a, int cpl_c, int cpl_d, int grid, hipStream_t s) {
+int decode_launch_fused_mlp(const FusedMlpArgs& fa, int grid, hipStream_t s) {
     if (fa.a.M <= 0) return LR_OK;
-    if (fa.a.M <= 16) return launch_mlp_cpl<1>(fa, cpl_a, cpl_c, cpl_d, grid, s);
-    return launch_mlp_cpl<2>(fa, cpl_a, cpl_c, cpl_d, grid, s);
+    return fa.a.M <= 16 ? launch_mlp<1>(fa, grid, s) : launch_mlp<2>(fa, grid, s);
 }
 
 }  // namespace lr

@@ -3,10 +3,10 @@
 
 namespace lr {
 
-template <int MB, int CPL>
-static int launch_stage_cfg(const DStage& st, bool a_f32, int epi, hipStream_t s) {
+template <int MB>
+static int launch_stage(const DStage& st, bool a_f32, int epi, hipStream_t s) {
     const dim3 grid((unsigned)st.total_tiles), block(256);
-    constexpr int PF = 3;
+    constexpr int PF = 3, CPL = 4;
     if (epi == EPI_ATOMIC) {
         if (a_f32) hipLaunchKernelGGL((k_decode_stage<MB, CPL, true, EPI_ATOMIC, PF>), grid, block, 0, s, st);
         else       hipLaunchKernelGGL((k_decode_stage<MB, CPL, false, EPI_ATOMIC, PF>), grid, block, 0, s, st);
@@ -20,13 +20,9 @@ static int launch_stage_cfg(const DStage& st, bool a_f32, int epi, hipStream_t s
     return launch_status("decode stage");
 }
 
-int decode_launch_stage(const DStage& st, int cpl, bool a_f32, int epi, hipStream_t s) {
+int decode_launch_stage(const DStage& st, bool a_f32, int epi, hipStream_t s) {
     if (st.total_tiles <= 0 || st.M <= 0) return LR_OK;
-    const int mb = st.M <= 16 ? 1 : 2;
-    if (mb == 1 && cpl == 4) return launch_stage_cfg<1, 4>(st, a_f32, epi, s);
-    if (mb == 2 && cpl == 4) return launch_stage_cfg<2, 4>(st, a_f32, epi, s);
-    set_error("bad decode tile configuration");
-    return LR_ERR_UNSUPPORTED;
+    return st.M <= 16 ? launch_stage<1>(st, a_f32, epi, s) : launch_stage<2>(st, a_f32, epi, s);
 }
 
 }  // namespace lr

@@ -19,9 +19,9 @@ bool decode_shape_ok(int64_t M, int64_t K, int64_t N) {
            K < (1 << 24) && N < (1 << 24);
 }
 
-// Columns per lane of every stage: 4 = 64-column tiles with 8-byte loads.  (128-column tiles with 16-byte loads
-// were measured slower: fewer, fatter tiles.)
-constexpr int kCpl = 4;
+// Columns of a tile of every stage: 4 per lane, 8-byte loads.  (128-column tiles with 16-byte loads were measured slower:
+// fewer, fatter tiles.)
+constexpr int kTileCols = 64;
 // Tiles of a split-K stage that runs as a launch of its own (device shared with other work, or accumulators too big).
 constexpr int kUnfusedTiles = 512;
 
@@ -57,9 +57,9 @@ struct Final { const void* T; int64_t r; const void* V; int64_t N; const void* b
 
 // t[M, ldc] += A[M, K] * W_i[K, N_i] for several weight matrices sharing A, split along K.
 static void build_splitk(DStage& st, const void* A, int64_t lda, int64_t M, int64_t K, const SplitK* items, int n,
-                         int64_t ldc, int64_t want_tiles, int cpl, DecodeForm form) {
+                         int64_t ldc, int64_t want_tiles, DecodeForm form) {
     st.nprob = n; st.M = (int)M;
-    const int nc = 16 * cpl;
+    constexpr int nc = kTileCols;
     int64_t n_tiles = 0;
     for (int i = 0; i < n; ++i) n_tiles += (items[i].N + nc - 1) / nc;
     const int ks = pick_ks(K, n_tiles, M, want_tiles);
@@ -76,10 +76,9 @@ static void build_splitk(DStage& st, const void* A, int64_t lda, int64_t M, int6
 }
 
 // y_i[M, N_i] = t_i[M, r_i] * V_i[r_i, N_i] + bias_i: full K per tile, the epilogue writes bf16.
-static int build_final(DStage& st, const Final* items, int n, int64_t ldt, int64_t M, DecodeForm form) {
+static void build_final(DStage& st, const Final* items, int n, int64_t ldt, int64_t M, DecodeForm form) {
     st.nprob = n; st.M = (int)M;
-    const int cpl = 4;   // 64-column tiles: full K per tile, so narrow tiles are the only source of parallelism
-    const int nc = 16 * cpl;
+    constexpr int nc = kTileCols;      // (full K per tile, so narrow tiles are the only source of parallelism)
     int tile = 0;
     for (int i = 0; i < n; ++i) {
         DProb& p = st.p[i]; zero_prob(p);
@@ -91,7 +90,6 @@ static int build_final(DStage& st, const Final* items, int n, int64_t ldt, int64
     }
     st.total_tiles = tile;
     set_wlayout(st, nc, form);
-    return cpl;
 }
 
 // One launch per call unless the device is shared with other work (lowrank_configure) or the device query fails.  The grid is one
@@ -119,7 +117,6 @@ static int run_two_stage(const void* x, int64_t d_in, int64_t M, const SplitK* s
     for (int i = 0; i < nf; ++i) factor_bytes += (size_t)fin_in[i].r * fin_in[i].N * 2;
     const int G = t_only ? 0 : fused_grid(factor_bytes);
     const bool fused = G > 0 && (size_t)M * R * 4 <= L.acc_bytes;
-    const int c1 = kCpl;
     float* tbase = fused ? (float*)L.acc0 : (float*)L.staging;
     SplitK sk[kMaxProb]; Final fin[kMaxProb];
     DStage s1, s2;
@@ -132,12 +129,12 @@ static int run_two_stage(const void* x, int64_t d_in, int64_t M, const SplitK* s
         const size_t off = (size_t)(uintptr_t)fin_in[i].T;
         fin[i] = fin_in[i]; fin[i].T = (const void*)(tbase + off);
     }
-    build_splitk(s1, x, d_in, M, d_in, sk, nb, R, fused ? G : kUnfusedTiles, c1, form);
-    const int c2 = build_final(s2, fin, nf, R, M, form);
+    build_splitk(s1, x, d_in, M, d_in, sk, nb, R, fused ? G : kUnfusedTiles, form);
+    build_final(s2, fin, nf, R, M, form);
     if (fused) {
         FusedCommon fc = {L.ctrl, L.acc0, L.acc_bytes, (uint32_t)(M * R), g_wait_limit, g_trace_buffer};
         if (form == DF_ANY) return decode_launch_fused2_rag(fc, s1, s2, G, s);
-        return decode_launch_fused2(fc, s1, s2, c1, c2, G, s);
+        return decode_launch_fused2(fc, s1, s2, G, s);
     }
     int st = fill_zero(tbase, (size_t)M * R * 4, s);
     if (st != LR_OK) return st;
@@ -145,9 +142,9 @@ static int run_two_stage(const void* x, int64_t d_in, int64_t M, const SplitK* s
         st = decode_launch_stage_rag(s1, false, EPI_ATOMIC, s);
         return st != LR_OK ? st : decode_launch_stage_rag(s2, true, EPI_STORE, s);
     }
-    st = decode_launch_stage(s1, c1, false, EPI_ATOMIC, s);
+    st = decode_launch_stage(s1, false, EPI_ATOMIC, s);
     if (st != LR_OK) return st;
-    return decode_launch_stage(s2, c2, true, EPI_STORE, s);
+    return decode_launch_stage(s2, true, EPI_STORE, s);
 }
 
 int decode_linear(const void* x, const void* U, const void* V, const void* bias, void* y,
@@ -200,8 +197,8 @@ int decode_mlp(const void* x, const void* U_gu, const void* V_g, const void* V_u
     const int64_t want = fused ? G : kUnfusedTiles;
     DStage sa, sb, sc, sd;
     const SplitK a = {U_gu, r_g + r_u, t}, c = {U_d, r_d, t + r_gu};
-    build_splitk(sa, x, d, M, d, &a, 1, r_all, want, kCpl, form);
-    build_splitk(sc, h, ffn, M, ffn, &c, 1, r_all, want, kCpl, form);
+    build_splitk(sa, x, d, M, d, &a, 1, r_all, want, form);
+    build_splitk(sc, h, ffn, M, ffn, &c, 1, r_all, want, form);
     {   // gate/up: both products of a 64-column tile in one workgroup, full K
         sb.nprob = 1; sb.M = (int)M;
         DProb& p = sb.p[0]; zero_prob(p);
@@ -209,12 +206,12 @@ int decode_mlp(const void* x, const void* U_gu, const void* V_g, const void* V_u
         p.W2 = (const bf16_t*)V_u; p.K2 = (int)r_u; p.lda2 = (int)r_all;
         p.A = t; p.A2 = t + r_g;
         p.N = (int)ffn; p.Y = h; p.bias = (const bf16_t*)b_g; p.bias2 = (const bf16_t*)b_u;
-        p.tiles_n = (int)((ffn + 63) / 64); p.KS = (int)r_g; p.tile_begin = 0;
+        p.tiles_n = (int)((ffn + kTileCols - 1) / kTileCols); p.KS = (int)r_g; p.tile_begin = 0;
         sb.total_tiles = p.tiles_n;
-        set_wlayout(sb, 64, form);
+        set_wlayout(sb, kTileCols, form);
     }
     Final f = {(const void*)(t + r_gu), r_d, V_d, d, b_d, out, {nullptr, nullptr, 0, 1}};
-    const int cd = build_final(sd, &f, 1, r_all, M, form);
+    build_final(sd, &f, 1, r_all, M, form);
     if (fused) {
         FusedMlpArgs fa;
         fa.fc = FusedCommon{L.ctrl, L.acc0, L.acc_bytes, (uint32_t)(M * r_all), g_wait_limit, g_trace_buffer};
@@ -222,7 +219,7 @@ int decode_mlp(const void* x, const void* U_gu, const void* V_g, const void* V_u
         DStageT<1>* dst[4] = {&fa.a, &fa.b, &fa.c, &fa.d};
         for (int i = 0; i < 4; ++i) { dst[i]->p[0] = src[i]->p[0]; dst[i]->nprob = 1; dst[i]->M = (int)M; dst[i]->total_tiles = src[i]->total_tiles; }
         if (any) return decode_launch_fused_mlp_rag(fa, G, s);
-        return decode_launch_fused_mlp(fa, kCpl, kCpl, cd, G, s);
+        return decode_launch_fused_mlp(fa, G, s);
     }
     int st = fill_zero(t, (size_t)M * r_all * 4, s);
     if (st != LR_OK) return st;
@@ -232,13 +229,13 @@ int decode_mlp(const void* x, const void* U_gu, const void* V_g, const void* V_u
         if (st == LR_OK) st = decode_launch_stage_rag(sc, true, EPI_ATOMIC, s);
         return st != LR_OK ? st : decode_launch_stage_rag(sd, true, EPI_STORE, s);
     }
-    st = decode_launch_stage(sa, kCpl, false, EPI_ATOMIC, s);
+    st = decode_launch_stage(sa, false, EPI_ATOMIC, s);
     if (st != LR_OK) return st;
-    st = decode_launch_stage(sb, 4, true, EPI_GATEUP, s);
+    st = decode_launch_stage(sb, true, EPI_GATEUP, s);
     if (st != LR_OK) return st;
-    st = decode_launch_stage(sc, kCpl, false, EPI_ATOMIC, s);
+    st = decode_launch_stage(sc, false, EPI_ATOMIC, s);
     if (st != LR_OK) return st;
-    return decode_launch_stage(sd, cd, true, EPI_STORE, s);
+    return decode_launch_stage(sd, true, EPI_STORE, s);
 }
 
 }  // namespace lr

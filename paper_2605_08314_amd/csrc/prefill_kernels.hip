@@ -947,7 +947,8 @@ static int launch_persist(PArgs a, hipStream_t s, bool share_k = false) {
     if constexpr (WG != 22) {
         hipLaunchKernelGGL((k_prefill_halves<BM, BN, WG>), dim3((unsigned)grid), dim3(TileWaves<BM, BN, WG>::NW * 64), 0, s, a);
     } else if constexpr (BM == 256) {
-        return launch_persist<BM, BN, BN == 256 ? 24 : 42, EPI, MINB>(a, s);          // K not shared after all
+        set_error("prefill gemm: a shared-K launch with too little work");            // (want_share_k asks for more)
+        return LR_ERR_UNSUPPORTED;
     } else {
         hipLaunchKernelGGL((k_prefill_persist<BM, BN, WG, EPI, MINB, false>), dim3((unsigned)grid), dim3(TileWaves<BM, BN, WG>::NW * 64), 0, s, a);
     }
