@@ -54,8 +54,22 @@ def test_product_of_few_tiles(G, M, K, N):
     assert torch.isnan(t[M]).all()
 
 
-@pytest.mark.parametrize("M,r_g,r_u,r_d", [(40, 128, 192, 128), (128, 256, 128, 192), (200, 64, 128, 64), (256, 768, 512, 256)])
+def runs_prefill_kernels(M, d, f, r_g, r_u, r_d):
+    """The rule of the tuned prefill products: K in 64-row steps, N in 128-column tiles, for all five factors."""
+    return all(k >= 64 and k % 64 == 0 and n >= 128 and n % 128 == 0 for k, n in ((d, r_g + r_u), (r_g, f), (r_u, f), (f, r_d), (r_d, d)))
+
+
+# K of gate/up at its shortest for two halves (128: two steps each), in odd steps per half (192, 320), unequal on the two sides, below
+# 128 on one side or both (one workgroup of four waves per tile then); row remainders.  The last three have ranks outside the rule
+# of the tuned kernels and run the any-size tile kernels.
+MLP_OF_FEW_TILES = [(40, 128, 128, 128), (129, 192, 192, 128), (200, 192, 320, 128), (128, 128, 256, 384), (100, 64, 64, 128), (77, 64, 192, 128), (256, 768, 512, 256),
+                    (40, 128, 192, 128), (128, 256, 128, 192), (200, 64, 128, 64)]
+
+
+@pytest.mark.parametrize("M,r_g,r_u,r_d", MLP_OF_FEW_TILES)
 def test_mlp_of_few_tiles(G, M, r_g, r_u, r_d):
+    assert runs_prefill_kernels(M, 512, 1408, r_g, r_u, r_d) == ((M, r_g, r_u, r_d) not in MLP_OF_FEW_TILES[-3:])
+    assert ((M + 127) // 128) * (1408 // 128) <= 256                 # gate/up: at most one tile per compute unit
     g = torch.Generator(device="cuda"); g.manual_seed(M)
     d, f = 512, 1408
     x = normal(g, M, d)

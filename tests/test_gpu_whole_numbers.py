@@ -304,3 +304,38 @@ def test_more_tiles_than_one_launch_has(G, kind):
         B.lowrank_qkv(x, U, V, None, y, None, "auto", B.new_workspace(B.LR_OP_QKV, M, 1, 8, 8, B.LR_BF16))
         for i in range(8):                                                        # 24-bit products: exact before the one rounding
             assert torch.equal(y[i], (x.float() * U[i].float() * V[i].float()).to(torch.bfloat16)), i
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_sizes_beyond_24_bits(G, oracle, dtype):
+    """Widths of 2^24 and more run the plain kernels, one thread per output element: layers, a cache, the hidden rows of an MLP."""
+    B = G.B
+    td, n = G.tdtype(dtype), (1 << 24) + 5
+    g = torch.Generator(device="cuda"); g.manual_seed(5)
+    w = lambda *s: torch.randn(s, device="cuda", dtype=td, generator=g)     # noqa: E731
+    x, U, V, b = w(2, 3), [w(3, 2), w(3, 2)], [w(2, n), w(2, n)], w(n)
+    want = [(x.double() @ U[i].double()).float().double() @ V[i].double() for i in range(2)]
+    y = torch.full((2, n), float("nan"), device="cuda", dtype=td)
+    B.lowrank_linear(x, U[0], V[0], b, y, "auto", B.new_workspace(B.LR_OP_LINEAR, 2, 3, 2, n, G.code(dtype)))
+    eps = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -23              # one rounding of the result (and of two terms in fp32)
+    close = lambda got, ref: torch.all((got.double() - ref).abs() <= eps * ref.abs() + 4 * eps * 2.0 ** -10)     # noqa: E731
+    assert close(y, want[0] + b.double())
+    kc, vc = (torch.full((2, 3, 1, n), 7.0, device="cuda", dtype=td) for _ in range(2))
+    pos = torch.tensor([0, 2], device="cuda", dtype=torch.int32)
+    B.lowrank_qkv(x, U, V, None, [y, None], dict(k_cache=kc, v_cache=vc, pos=pos, tokens_per_seq=1, k_index=0, v_index=1), "auto",
+                  B.new_workspace(B.LR_OP_QKV, 2, 3, 4, 2 * n, G.code(dtype)))
+    assert close(y, want[0])
+    for c, ref in ((kc, want[0]), (vc, want[1])):
+        assert close(c[0, 0, 0], ref[0]) and close(c[1, 2, 0], ref[1])
+        assert (c[0, 1:] == 7.0).all() and (c[1, :2] == 7.0).all()
+    del kc, vc, y, want
+    # the hidden rows are read back through a down factor that takes up three of them, the last one included
+    U_gu, V_g, V_u, U_d, V_d = w(3, 4), w(2, n), w(2, n), torch.zeros((n, 3), device="cuda", dtype=td), torch.eye(3, device="cuda", dtype=td)
+    at = [0, 12345678, n - 1]
+    for i, k in enumerate(at):
+        U_d[k, i] = 1.0
+    out = torch.full((2, 3), float("nan"), device="cuda", dtype=td)
+    B.lowrank_packed_mlp(x, U_gu, V_g, V_u, U_d, V_d, None, None, None, out, "auto", B.new_workspace(B.LR_OP_PACKED_MLP, 2, 3, 7, n, G.code(dtype)))
+    t = x.double() @ U_gu.double()
+    h = torch.nn.functional.silu(t[:, :2] @ V_g[:, at].double()) * (t[:, 2:] @ V_u[:, at].double())
+    assert torch.all((out.double() - h).abs() <= 16 * eps * h.abs().max())
