@@ -43,8 +43,11 @@
  *              lowrank_configure(LR_CFG_DEVICE_SHARED, 1); calls then use one launch per stage and no
  *              cross-workgroup waits.  If the guarantee is broken anyway, the waits are bounded: a
  *              workgroup that gives up writes NaN as its part of the result and raises the error word
- *              of the workspace, every later call on that workspace returns NaN results until it is
+ *              of the workspace, every later decode call on that workspace returns NaN results until it is
  *              prepared again (lowrank_workspace_init), and lowrank_workspace_status reports it.
+ *   Repeats    The decode kernels (bf16, up to 32 rows) add partial sums with fp32 atomics in the order in which they arrive: a
+ *              call repeated on the same operands may differ from itself as another order of summation would.  Every other
+ *              call repeats bit for bit.
  *   Errors     Return value is an lr_status: 0 on success, negative on error.  On a validation
  *              error nothing is launched.  lowrank_last_error() gives a thread-local message.
  *              No C++ exception crosses this boundary.
@@ -110,7 +113,8 @@ int lowrank_linear(const void *x, const void *U, const void *V, const void *bias
  * Nothing is allocated or freed, here or in any routine it calls.  Up to 32 rows of bf16 run the
  * decode kernels as one launch per stage (no cross-workgroup waits, so no residency requirement), everything else the
  * any-size tile kernels.  All calls on one GPU share that GPU's scratch area: calls that overlap in time on one
- * GPU race, even on different streams; order them.  The area is cleared on the stream at the start of each call.
+ * GPU race, even on different streams; order them.  A call needs nothing from the area's contents: the decode kernels
+ * clear it on the stream first, the tile kernels write what they read.
  */
 int lowrank_linear_noalloc(const void *x, const void *U, const void *V, const void *bias /* nullable */,
                            void *y, int64_t M, int64_t d_in, int64_t r, int64_t d_out,
@@ -290,9 +294,9 @@ typedef enum { LR_CFG_DEVICE_SHARED = 0, LR_CFG_WAIT_LIMIT = 1 } lr_config;
 int lowrank_configure(int option, int64_t value);
 
 /*
- * Name of the kernel family the dispatcher picks for a call of this shape, e.g.
- * "decode_mfma", "prefill_mfma", "generic" (pure host function; static storage); with LR_BF16_PANELS
- * "decode_mfma" or "unsupported".
+ * Which rule a call of this shape meets (pure host function; static storage): "decode_mfma" or "prefill_mfma", the kernels
+ * tuned for regular sizes, or "generic", everything else -- bf16 calls of other sizes or alignments, fp32 calls and sizes of
+ * 2^24 and more, whatever kernels run them (see Sizes above); with LR_BF16_PANELS "decode_mfma" or "unsupported".
  * `aligned` is nonzero when every pointer of the call is 16-byte aligned.
  */
 const char *lowrank_plan_name(int op, int64_t M, int64_t d_in, int64_t r_total, int64_t d_out,

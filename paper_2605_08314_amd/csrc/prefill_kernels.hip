@@ -958,9 +958,12 @@ static int launch_persist(PArgs a, hipStream_t s, bool share_k = false) {
 // Tile shape of a plain launch, from a small cost model fitted to measurements on this chip (300 .. 8192 rows, K = 256 .. 4096,
 // 1152 .. 15360 columns), in units of "a full round of 256 x 256 tiles, one per CU" (K = 512: 15 us and 5 us for the launch).
 // A last round of up to 128 tiles takes 0.72 of that.  128 x 128 tiles take 0.64 per round of two on every CU, 0.46 where every
-// tile has a CU to itself from the start and 0.36 as the last round.  256 x 192 tiles hardly save the time of the columns they
-// leave out (8192 x 4096 x 1536: 97 us, as 256 x 256 88): their weight keeps them to the widths 1152 and 1536 at 8192 rows, where
-// they are an answer of lowrank_prefill_tile that callers rely on.
+// tile has a CU to itself from the start and 0.36 as the last round.
+// 256 x 192 tiles pay where 256-wide ones would compute columns that do not exist: three products of 384 columns over 8192 x
+// 4096 take 89 us, as 256 x 256 98.  Where both cover the columns they are 3-7 % slower (8192 x 4096 x 1536 95 us against 89,
+// 4096 x 768 x 3072 24.6 against 23.3, 1024 x 512 x 12288 18.7 against 17.8); their weight of 0.85 for a round, full or not, yet
+// chooses them there when they fill their rounds and 256 x 256 leaves a quarter of one empty.  lowrank_prefill_tile has always
+// answered so; 0.92 of the same function of the rounds as for 256 x 256 would give the measured order.
 static int pick_tile(const PArgs& a) {
     long t256 = 0, t192 = 0, t128 = 0;
     for (int i = 0; i < a.nprob; ++i) {
