@@ -530,13 +530,13 @@ __device__ __forceinline__ void wave_epilogue(const f32x16_t (&acc)[(TileWaves<B
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int cc = 0; cc < 3; ++cc) {
-                        const float w = c + cc < part1 ? 1.f : 0.f;
+                        if (c + cc >= part1) continue;                            // (uniform; zero times a repeated slot would be NaN for an infinite sum)
 #pragma unroll
                         for (int p2 = 0; p2 < np2; ++p2)
 #pragma unroll
                             for (int vg = 0; vg < 4; ++vg) {
-                                psum[p2][vg][0] += w * __uint_as_float(raw[cc][p2][vg][0].x); psum[p2][vg][1] += w * __uint_as_float(raw[cc][p2][vg][0].y);
-                                psum[p2][vg][2] += w * __uint_as_float(raw[cc][p2][vg][1].x); psum[p2][vg][3] += w * __uint_as_float(raw[cc][p2][vg][1].y);
+                                psum[p2][vg][0] += __uint_as_float(raw[cc][p2][vg][0].x); psum[p2][vg][1] += __uint_as_float(raw[cc][p2][vg][0].y);
+                                psum[p2][vg][2] += __uint_as_float(raw[cc][p2][vg][1].x); psum[p2][vg][3] += __uint_as_float(raw[cc][p2][vg][1].y);
                             }
                     }
                 }

@@ -107,3 +107,23 @@ def test_cache_rows_and_bias(G, n, T, past):
             p = int(pos[i])
             assert torch.equal(cache[i, :p], old[i, :p]) and torch.equal(cache[i, p + T:], old[i, p + T:])
             check(cache[i, p:p + T].reshape(T, d), w[i * T:(i + 1) * T])
+
+
+@pytest.mark.parametrize("M,K,N,tile", [(4096, 8192, 1536, (256, 192, 1)), (8192, 4096, 1536, (256, 192, 0)), (3000, 384, 4096, (256, 256, 0)), (512, 768, 4096, (128, 128, 0)),
+                                        (512, 4096, 1536, (128, 128, 5))])
+def test_infinite_weights(G, M, K, N, tile):
+    """An infinite weight makes its column infinite, with the sign of the row's value, in every form of the product: also where K is shared
+    between workgroups or cut into chunks, whichever part it falls into."""
+    assert G.B.lowrank_prefill_tile(M, K, N, 1) == tile
+    g = torch.Generator(device="cuda"); g.manual_seed(M + K)
+    x, U = normal(g, M, K), normal(g, K, N)
+    at = {3: 0, 130: K // 2 + 5, 700: K - 1, N - 1: 77}
+    for n, k in at.items():
+        U[k, n] = float("inf")
+    t = torch.empty((M, N), device="cuda", dtype=torch.bfloat16)
+    G.B.lowrank_rank_project(x, U, t, G.B.new_workspace(G.B.LR_OP_LINEAR, M, K, N, 0, G.B.LR_BF16))
+    torch.cuda.synchronize()
+    for n, k in at.items():
+        assert torch.equal(t[:, n].float(), x[:, k].float() * float("inf"))        # (NaN for a zero in x: equal() refuses NaN, and randn has none)
+    rest = [n for n in range(N) if n not in at]
+    check(t[:, rest], (x.float() @ U[:, rest].float()))
